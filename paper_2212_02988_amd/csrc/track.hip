@@ -13,68 +13,91 @@
 
 namespace prism {
 
-// The rows of observed pixel p (row-major index): geometric row 0
-// (point-to-plane against the nearest anchor pixel) and colour rows 1-3
-// (bilinear anchor colour minus the observation), residuals in double
-// precision, Jacobians w.r.t. the pose perturbation in single precision.
-// rm: bit 0 the geometric row passed its gate, bit 1 the colour rows.
-// D and orgb: the pixel's observed depth and colour (loaded by the caller).
-__device__ __forceinline__ void p2_pixel(const CamC& c, const CamD& cd, const Rel32& rel, int p, float D,
-                                         const float orgb[3], const float* __restrict__ a_depth,
-                                         const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
-                                         const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
-                                         const WeightsC& wt, float J[4][6], double r[4], int& rm) {
-    const int u = p % c.W, v = p / c.W;
+// three floats at a 4-byte aligned address, one load
+typedef float float3u __attribute__((ext_vector_type(3), aligned(4)));
+
+// column and row of pixel p (< 2^26): the quotient by a single-precision
+// reciprocal is off by at most one (rows are below 2^13) and is corrected; a
+// division by a run-time width takes about three times the instructions
+__device__ __forceinline__ void pixel_uv(int W, int p, int& u, int& v) {
+    v = (int)((float)p * __builtin_amdgcn_rcpf((float)W));
+    u = p - v * W;
+    const int under = u < 0 ? 1 : 0, over = u >= W ? 1 : 0;
+    u += (under - over) * W;
+    v += over - under;
+}
+
+// anchor values at a pixel's two associations
+struct AnchorTaps {
+    float depth, n[3];     // nearest pixel
+    float rgb[4][3];       // bilinear corners (0,0), (1,0), (0,1), (1,1)
+};
+
+// the bilinear corners from pixel q00, dx to the right and dy below, in elements
+__device__ __forceinline__ void load_corners(const float* __restrict__ a_rgb, int q00, int dx, int dy,
+                                             AnchorTaps& t) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        r[a] = 0.0;
+    for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int m = 0; m < 6; ++m) J[a][m] = 0.0f;
-    }
-    rm = 0;
-    if (!depth_ok(D)) return;
+        for (int s = 0; s < 2; ++s) {
+            const float3u v = *reinterpret_cast<const float3u*>(a_rgb + 3 * (q00 + r * dy + s * dx));
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) t.rgb[2 * r + s][ch] = v[ch];
+        }
+}
+
+// Associations of an observed pixel in the fixed single-precision recipe:
+// nearest anchor pixel q (geo) and bilinear base pixel q00 = biy W + bix (pho);
+// without an association the indices are 0.
+struct Assoc {
+    bool geo, pho;
+    int giu, giv, bix, biy, q, q00;
+};
+
+__device__ __forceinline__ Assoc p2_assoc(const CamC& c, const Rel32& rel, int u, int v, float D) {
+    Assoc o{false, false, 0, 0, 0, 0, 0, 0};
     float rx = ((float)u + 0.5f - c.cx) * c.ifx;
     float ry = ((float)v + 0.5f - c.cy) * c.ify;
     float X[3] = {D * rx, D * ry, D};
     float Y[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) Y[a] = ((rel.R[a][0] * X[0] + rel.R[a][1] * X[1]) + rel.R[a][2] * X[2]) + rel.t[a];
-    bool geo = false, pho = false;
-    int giu = 0, giv = 0, bix = 0, biy = 0;
-    float uu = 0.0f, vv = 0.0f;
-    if (Y[2] > 0.0f) {
-        uu = c.fx * (Y[0] / Y[2]) + c.cx;
-        vv = c.fy * (Y[1] / Y[2]) + c.cy;
+    if (depth_ok(D) && Y[2] > 0.0f) {
+        const float uu = c.fx * (Y[0] / Y[2]) + c.cx, vv = c.fy * (Y[1] / Y[2]) + c.cy;
         if (uu >= 0.0f && uu < (float)c.W && vv >= 0.0f && vv < (float)c.H) {
-            giu = (int)uu;
-            giv = (int)vv;
-            geo = true;
+            o.giu = (int)uu;
+            o.giv = (int)vv;
+            o.geo = true;
         }
-        float bx = uu - 0.5f, by = vv - 0.5f;
+        const float bx = uu - 0.5f, by = vv - 0.5f;
         if (bx >= 0.0f && bx < (float)(c.W - 1) && by >= 0.0f && by < (float)(c.H - 1)) {
-            bix = (int)bx;
-            biy = (int)by;
-            pho = true;
+            o.bix = (int)bx;
+            o.biy = (int)by;
+            o.pho = true;
         }
     }
-    if (geo) {
-        int q = giv * c.W + giu;
-        geo = a_mask[q] && a_nmask[q];
-    }
-    int q00 = biy * c.W + bix;
-    if (pho) pho = a_mask[q00] && a_mask[q00 + 1] && a_mask[q00 + c.W] && a_mask[q00 + c.W + 1];
-    if (!(geo || pho)) return;
-    {
-    // the value path may fuse multiplies and adds: the pixel decisions above
-    // stay in the fixed single-precision recipe; the residual gates below
-    // compare double-precision values, which differ from the oracle's by
-    // rounding either way
+    o.q = o.giv * c.W + o.giu;
+    o.q00 = o.biy * c.W + o.bix;
+    return o;
+}
+
+// The value path may fuse multiplies and adds: the pixel decisions stay in the
+// fixed single-precision recipe; the residual gates compare double-precision
+// values, which differ from the oracle's by rounding either way.
+
+// back-projected point in the anchor camera (double precision) and its
+// derivative w.r.t. the pose perturbation (single precision)
+struct Moved {
+    double Y[3];
+    float dY[3][6];
+};
+
+__device__ __forceinline__ Moved p2_moved(const CamD& cd, const Rel32& rel, int u, int v, float D) {
 #pragma clang fp contract(fast)
-    // values in double precision: back-projected point, moved into the
-    // anchor camera; Jacobians in single precision
+    Moved o;
     const Pose64& Pc = rel.cur;
     const Pose64& Pp = rel.prev;
-    double rc[3], Xd[3], RXd[3], dW[3], Yd[3];
+    double rc[3], Xd[3], RXd[3], dW[3];
     pixel_dir64(cd, u, v, rc);
 #pragma unroll
     for (int a = 0; a < 3; ++a) Xd[a] = (double)D * rc[a];
@@ -83,69 +106,147 @@ __device__ __forceinline__ void p2_pixel(const CamC& c, const CamD& cd, const Re
 #pragma unroll
     for (int a = 0; a < 3; ++a) dW[a] = RXd[a] + Pc.t[a] - Pp.t[a];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) Yd[a] = Pp.R[0][a] * dW[0] + Pp.R[1][a] * dW[1] + Pp.R[2][a] * dW[2];
+    for (int a = 0; a < 3; ++a) o.Y[a] = Pp.R[0][a] * dW[0] + Pp.R[1][a] * dW[1] + Pp.R[2][a] * dW[2];
     // dY/ddelta = Rp^T [I | -[R X]x]
     float RX[3] = {(float)RXd[0], (float)RXd[1], (float)RXd[2]};
-    float dY[3][6];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         float e0 = (float)Pp.R[0][a], e1 = (float)Pp.R[1][a], e2 = (float)Pp.R[2][a];
-        dY[a][0] = e0;
-        dY[a][1] = e1;
-        dY[a][2] = e2;
-        dY[a][3] = fmaf(RX[1], e2, -RX[2] * e1);
-        dY[a][4] = fmaf(RX[2], e0, -RX[0] * e2);
-        dY[a][5] = fmaf(RX[0], e1, -RX[1] * e0);
+        o.dY[a][0] = e0;
+        o.dY[a][1] = e1;
+        o.dY[a][2] = e2;
+        o.dY[a][3] = fmaf(RX[1], e2, -RX[2] * e1);
+        o.dY[a][4] = fmaf(RX[2], e0, -RX[0] * e2);
+        o.dY[a][5] = fmaf(RX[0], e1, -RX[1] * e0);
     }
-    if (geo) {
-        int q = giv * c.W + giu;
-        double ra[3];
-        pixel_dir64(cd, giu, giv, ra);
-        double da = (double)a_depth[q];
-        double n0 = a_normals[3 * q], n1 = a_normals[3 * q + 1], n2 = a_normals[3 * q + 2];
-        double rg = n0 * (da * ra[0] - Yd[0]) + n1 * (da * ra[1] - Yd[1]) + n2 * (da * ra[2] - Yd[2]);
-        r[0] = rg;
-        float fn0 = (float)n0, fn1 = (float)n1, fn2 = (float)n2;
+    return o;
+}
+
+// geometric row: point-to-plane against the nearest anchor pixel
+__device__ __forceinline__ void p2_geo_row(const CamD& cd, const Moved& m, const Assoc& as, const AnchorTaps& tap,
+                                           float J[6], double& r) {
+#pragma clang fp contract(fast)
+    double ra[3];
+    pixel_dir64(cd, as.giu, as.giv, ra);
+    double da = (double)tap.depth;
+    double n0 = tap.n[0], n1 = tap.n[1], n2 = tap.n[2];
+    r = n0 * (da * ra[0] - m.Y[0]) + n1 * (da * ra[1] - m.Y[1]) + n2 * (da * ra[2] - m.Y[2]);
+    float fn0 = (float)n0, fn1 = (float)n1, fn2 = (float)n2;
 #pragma unroll
-        for (int m = 0; m < 6; ++m) J[0][m] = -fmaf(fn2, dY[2][m], fmaf(fn1, dY[1][m], fn0 * dY[0][m]));
-        if (fabs(rg) <= wt.gate_depth) rm |= 1;
+    for (int q = 0; q < 6; ++q) J[q] = -fmaf(fn2, m.dY[2][q], fmaf(fn1, m.dY[1][q], fn0 * m.dY[0][q]));
+}
+
+// colour rows: bilinear anchor colour minus the observation; returns
+// |r_r| + |r_g| + |r_b|
+__device__ __forceinline__ double p2_colour_rows(const CamC& c, const CamD& cd, const Moved& m, const Assoc& as,
+                                                 const AnchorTaps& tap, const float orgb[3], float J[3][6],
+                                                 double r[3]) {
+#pragma clang fp contract(fast)
+    const double izd = 1.0 / m.Y[2];
+    double ud = cd.fx * m.Y[0] * izd + cd.cx;
+    double vd = cd.fy * m.Y[1] * izd + cd.cy;
+    double ax = (ud - 0.5) - (double)as.bix, ay = (vd - 0.5) - (double)as.biy;
+    float Y2 = (float)m.Y[2];
+    float iz = 1.0f / Y2;
+    float du_[3] = {c.fx * iz, 0.0f, -c.fx * (float)m.Y[0] * iz * iz};
+    float dv_[3] = {0.0f, c.fy * iz, -c.fy * (float)m.Y[1] * iz * iz};
+    float dum[6], dvm[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        dum[q] = fmaf(du_[2], m.dY[2][q], du_[0] * m.dY[0][q]);
+        dvm[q] = fmaf(dv_[2], m.dY[2][q], dv_[1] * m.dY[1][q]);
+    }
+    double l1 = 0.0;
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+        double I00 = tap.rgb[0][ch], I10 = tap.rgb[1][ch], I01 = tap.rgb[2][ch], I11 = tap.rgb[3][ch];
+        // bilinear value and its image gradient as linear blends (fused
+        // multiply-adds; the same interpolant as the hat-weight sum, to
+        // rounding): rows blended along x, then the rows along y
+        const double d0 = I10 - I00, d1 = I11 - I01;
+        const double t0 = __builtin_fma(ax, d0, I00), t1 = __builtin_fma(ax, d1, I01);
+        double Ii = __builtin_fma(ay, t1 - t0, t0);
+        float gu = (float)__builtin_fma(ay, d1 - d0, d0);
+        float gv = (float)(t1 - t0);
+        double rp = Ii - (double)orgb[ch];
+        r[ch] = rp;
+        l1 += fabs(rp);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) J[ch][q] = fmaf(gv, dvm[q], gu * dum[q]);
+    }
+    return l1;
+}
+
+// The rows of an observed pixel (column u, row v): geometric row 0 and colour
+// rows 1-3, residuals in double precision, Jacobians in single precision.
+// rm: bit 0 the geometric row passed its gate, bit 1 the colour rows.
+// D and orgb: the pixel's observed depth and colour (loaded by the caller).
+// Masks first, then the anchor values they admit: fewest loads and registers,
+// for a GPU full of wavefronts.
+__device__ __forceinline__ void p2_pixel(const CamC& c, const CamD& cd, const Rel32& rel, int u, int v, float D,
+                                         const float orgb[3], const float* __restrict__ a_depth,
+                                         const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
+                                         const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
+                                         const WeightsC& wt, float J[4][6], double r[4], int& rm) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        r[a] = 0.0;
+#pragma unroll
+        for (int m = 0; m < 6; ++m) J[a][m] = 0.0f;
+    }
+    rm = 0;
+    const Assoc as = p2_assoc(c, rel, u, v, D);
+    const bool geo = as.geo && a_mask[as.q] && a_nmask[as.q];
+    const bool pho = as.pho && a_mask[as.q00] && a_mask[as.q00 + 1] && a_mask[as.q00 + c.W] && a_mask[as.q00 + c.W + 1];
+    if (!(geo || pho)) return;
+    const Moved m = p2_moved(cd, rel, u, v, D);
+    AnchorTaps tap;
+    if (geo) {
+        tap.depth = a_depth[as.q];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) tap.n[a] = a_normals[3 * as.q + a];
+        p2_geo_row(cd, m, as, tap, J[0], r[0]);
+        if (fabs(r[0]) <= wt.gate_depth) rm |= 1;
     }
     if (pho) {
-        const double izd = 1.0 / Yd[2];
-        double ud = cd.fx * Yd[0] * izd + cd.cx;
-        double vd = cd.fy * Yd[1] * izd + cd.cy;
-        double ax = (ud - 0.5) - (double)bix, ay = (vd - 0.5) - (double)biy;
-        float Y2 = (float)Yd[2];
-        float iz = 1.0f / Y2;
-        float du_[3] = {c.fx * iz, 0.0f, -c.fx * (float)Yd[0] * iz * iz};
-        float dv_[3] = {0.0f, c.fy * iz, -c.fy * (float)Yd[1] * iz * iz};
-        float dum[6], dvm[6];
-#pragma unroll
-        for (int m = 0; m < 6; ++m) {
-            dum[m] = fmaf(du_[2], dY[2][m], du_[0] * dY[0][m]);
-            dvm[m] = fmaf(dv_[2], dY[2][m], dv_[1] * dY[1][m]);
-        }
-        double l1 = 0.0;
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            double I00 = a_rgb[3 * q00 + ch], I10 = a_rgb[3 * (q00 + 1) + ch];
-            double I01 = a_rgb[3 * (q00 + c.W) + ch], I11 = a_rgb[3 * (q00 + c.W + 1) + ch];
-            // bilinear value and its image gradient as linear blends (fused
-            // multiply-adds; the same interpolant as the hat-weight sum, to
-            // rounding): rows blended along x, then the rows along y
-            const double d0 = I10 - I00, d1 = I11 - I01;
-            const double t0 = __builtin_fma(ax, d0, I00), t1 = __builtin_fma(ax, d1, I01);
-            double Ii = __builtin_fma(ay, t1 - t0, t0);
-            float gu = (float)__builtin_fma(ay, d1 - d0, d0);
-            float gv = (float)(t1 - t0);
-            double rp = Ii - (double)orgb[ch];
-            r[1 + ch] = rp;
-            l1 += fabs(rp);
-#pragma unroll
-            for (int m = 0; m < 6; ++m) J[1 + ch][m] = fmaf(gv, dvm[m], gu * dum[m]);
-        }
-        if (l1 <= wt.gate_rgb) rm |= 2;
+        load_corners(a_rgb, as.q00, 1, c.W, tap);
+        if (p2_colour_rows(c, cd, m, as, tap, orgb, J + 1, r + 1) <= wt.gate_rgb) rm |= 2;
     }
+}
+
+// The pixel's share of the gradient sum w r J, added to g, with every anchor
+// value loaded at once and no branch: one memory round trip, covered by the
+// arithmetic that does not need the anchor (for a wavefront that has nothing
+// else to run meanwhile).  Pixels without an association read pixel 0.
+__device__ __forceinline__ void p2_grad(const CamC& c, const CamD& cd, const Rel32& rel, int u, int v, float D,
+                                        const float orgb[3], const float* __restrict__ a_depth,
+                                        const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
+                                        const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
+                                        const WeightsC& wt, double g[6]) {
+    const Assoc as = p2_assoc(c, rel, u, v, D);
+    const int dx = as.pho ? 1 : 0, dy = as.pho ? c.W : 0;
+    const int m0 = a_mask[as.q], m1 = a_nmask[as.q], m2 = a_mask[as.q00], m3 = a_mask[as.q00 + dx],
+              m4 = a_mask[as.q00 + dy], m5 = a_mask[as.q00 + dy + dx];
+    AnchorTaps tap;
+    tap.depth = a_depth[as.q];
+    const float3u n = *reinterpret_cast<const float3u*>(a_normals + 3 * as.q);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) tap.n[a] = n[a];
+    load_corners(a_rgb, as.q00, dx, dy, tap);
+    const Moved m = p2_moved(cd, rel, u, v, D);
+    float J[4][6];
+    double r[4];
+    p2_geo_row(cd, m, as, tap, J[0], r[0]);
+    const double l1 = p2_colour_rows(c, cd, m, as, tap, orgb, J + 1, r + 1);
+    const bool geo = as.geo & (m0 != 0) & (m1 != 0) & (fabs(r[0]) <= wt.gate_depth);
+    const bool pho = as.pho & (m2 != 0) & (m3 != 0) & (m4 != 0) & (m5 != 0) & (l1 <= wt.gate_rgb);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        const double ag = wt.w_depth * r[0] * (double)J[0][q];
+        double ac = wt.w_rgb * r[1] * (double)J[1][q];
+        ac += wt.w_rgb * r[2] * (double)J[2][q];
+        ac += wt.w_rgb * r[3] * (double)J[3][q];
+        g[q] += (geo ? ag : 0.0) + (pho ? ac : 0.0);
     }
 }
 
@@ -189,8 +290,10 @@ __device__ __forceinline__ void track_p2_block(int blk, const CamC& c, const Cam
         float J[4][6];
         double r[4];
         int rm;
+        int u, v;
+        pixel_uv(c.W, p, u, v);
         const float orgb[3] = {obs_rgb[3 * p], obs_rgb[3 * p + 1], obs_rgb[3 * p + 2]};
-        p2_pixel(c, cd, rel, p, obs_depth[p], orgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, wt, J, r, rm);
+        p2_pixel(c, cd, rel, u, v, obs_depth[p], orgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, wt, J, r, rm);
         if (rm & 1) neq_add32(pacc, J[0], (float)r[0], row_weight(wt, false, r[0]));
         if (rm & 2)
 #pragma unroll
@@ -240,7 +343,7 @@ __global__ __launch_bounds__(256) void k_track_p2_batch(BatchArgs b) {
 // ---------------------------------------------------------------------------
 // the paper's pose optimiser: Adam without momentum on sampled pixels
 // ---------------------------------------------------------------------------
-// One workgroup runs the whole optimisation: at each step the 256 threads
+// One workgroup runs the whole optimisation: at each step 256 threads
 // evaluate the objective's rows on that step's sampled pixels (row-major
 // indices; an index outside the image is a pixel without rows; repeated
 // indices count repeatedly) at the current iterate, the gradient
@@ -250,181 +353,254 @@ __global__ __launch_bounds__(256) void k_track_p2_batch(BatchArgs b) {
 // bias-corrected vhat = v / (1 - b2^k), delta = -lr g / (sqrt(vhat) + eps),
 // iterate <- retract(iterate, delta).  scale = image pixels / sampled pixels
 // makes each step's data term an unbiased estimate of the full-image sum.
-// The serial part of a step is kept short: the prior term Lp e is formed by
-// the last thread while the others evaluate pixels, the six components'
-// moments by six lanes, and the iterate is carried as a rotation matrix
-// (converted back to a quaternion once, at the end).
+//
+// The steps are one dependent chain, so a step's latency is all that counts:
+//  * a fifth wavefront forms the prior term Lp e while four evaluate pixels
+//    (on one of their lanes it came after its pixel, in series);
+//  * a pixel's anchor values are loaded at once and covered by the arithmetic
+//    that does not need them; the next step's observations and the indices of
+//    the step after it are requested once they have arrived;
+//  * the six sums are reduced in registers, and every wavefront takes the
+//    step redundantly on its own copy of the iterate (a rotation matrix,
+//    converted back to a quaternion once, at the end), so a step has one
+//    workgroup barrier and nothing is handed out through memory after it.
+// 1000 steps of 200 pixels on a 320x240 frame: 5.6 -> 2.5 ms, about 5900
+// clocks a step, of which the pixel's chain takes 4100, the sums 700 and the
+// step 1250.  (Fetching the samples in the prior's wavefront took 3.1 ms: it
+// then ends last.)
 // Skipped when the prediction already fell back (improper prior).
+constexpr int kAdamThreads = 320;   // four wavefronts of pixels, one for the prior
 
-// Exp of a rotation vector; the series of sin(th)/th and (1 - cos(th))/th^2
-// to th^8 is exact in double precision below th = 0.01
-__device__ inline void so3_exp_step(const double w[3], double E[9]) {
-    const double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-    if (th2 >= 1e-4) {
-        so3_exp(w, E, nullptr);
-        return;
-    }
-    const double A = 1.0 - th2 / 6.0 * (1.0 - th2 / 20.0 * (1.0 - th2 / 42.0 * (1.0 - th2 / 72.0)));
-    const double B = 0.5 * (1.0 - th2 / 12.0 * (1.0 - th2 / 30.0 * (1.0 - th2 / 56.0 * (1.0 - th2 / 90.0))));
-    double K[9], K2[9];
-    skew(w, K);
-    mat3mul(K, K, K2);
-    for (int i = 0; i < 9; ++i) E[i] = A * K[i] + B * K2[i];
-    E[0] += 1.0;
-    E[4] += 1.0;
-    E[8] += 1.0;
+// Exp of a rotation vector.  The series of A = sin(th)/th and
+// B = (1 - cos(th))/th^2 to th^8 is exact in double precision below th = 0.01;
+// the functions of a larger angle stay out of the loop's straight-line code.
+struct SinCosC {
+    double A, B;
+};
+static __device__ __attribute__((noinline)) SinCosC so3_coef_far(double th2) {
+    const double th = sqrt(th2);
+    return SinCosC{sin(th) / th, (1.0 - cos(th)) / th2};
 }
 
-__global__ __launch_bounds__(256) void k_pose_adam(prism_filter_state* __restrict__ S, CamC c, CamD cd,
-                                                   const float* __restrict__ obs_depth,
-                                                   const float* __restrict__ obs_rgb,
-                                                   const float* __restrict__ a_depth,
-                                                   const float* __restrict__ a_rgb,
-                                                   const uint8_t* __restrict__ a_mask,
-                                                   const float* __restrict__ a_normals,
-                                                   const uint8_t* __restrict__ a_nmask, WeightsC wt,
-                                                   const int32_t* __restrict__ pixels, AdamC ad) {
-    __shared__ Rel32 srel;   // cur: the iterate (double R, t); prev: the anchor pose
-    __shared__ double red[4][6];
-    __shared__ double lpe[6];
-    __shared__ double Rp[9], tp[3];
-    __shared__ double Lp[36];
+__device__ inline void so3_exp_step(const double w[3], double E[9]) {
+    const double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+    constexpr double i6 = 1.0 / 6.0, i20 = 1.0 / 20.0, i42 = 1.0 / 42.0, i72 = 1.0 / 72.0;
+    constexpr double i12 = 1.0 / 12.0, i30 = 1.0 / 30.0, i56 = 1.0 / 56.0, i90 = 1.0 / 90.0;
+    double A = 1.0 - th2 * i6 * (1.0 - th2 * i20 * (1.0 - th2 * i42 * (1.0 - th2 * i72)));
+    double B = 0.5 * (1.0 - th2 * i12 * (1.0 - th2 * i30 * (1.0 - th2 * i56 * (1.0 - th2 * i90))));
+    if (th2 >= 1e-4) {
+        const SinCosC f = so3_coef_far(th2);
+        A = f.A;
+        B = f.B;
+    }
+    // E = I + A [w]x + B [w]x^2, with [w]x^2 = w w^T - th2 I
+    const double Bw[3] = {B * w[0], B * w[1], B * w[2]};
+    const double d = 1.0 - B * th2;
+    E[0] = __builtin_fma(Bw[0], w[0], d);
+    E[4] = __builtin_fma(Bw[1], w[1], d);
+    E[8] = __builtin_fma(Bw[2], w[2], d);
+    const double xy = Bw[0] * w[1], xz = Bw[0] * w[2], yz = Bw[1] * w[2];
+    E[1] = __builtin_fma(-A, w[2], xy);
+    E[3] = __builtin_fma(A, w[2], xy);
+    E[2] = __builtin_fma(A, w[1], xz);
+    E[6] = __builtin_fma(-A, w[1], xz);
+    E[5] = __builtin_fma(-A, w[0], yz);
+    E[7] = __builtin_fma(A, w[0], yz);
+}
+
+// x + the value of the lane a DPP control selects
+template <int Ctrl>
+__device__ __forceinline__ double add_dpp(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), Ctrl, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), Ctrl, 0xF, 0xF, false);
+    return x + __hiloint2double(hi, lo);
+}
+
+// Six sums over a wavefront without LDS: the 32-lane swap hands lanes 0-31
+// the sums of values 0-2 and lanes 32-63 those of 3-5, the row swap and four
+// DPP steps finish each half; s[0..2] are the same in every lane of a half.
+__device__ __forceinline__ void wave_sum6(const double g[6], double s[3]) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(g[j]),
+                                                        (unsigned)__double2loint(g[j + 3]), false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(g[j]),
+                                                        (unsigned)__double2hiint(g[j + 3]), false, false);
+        s[j] = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const unsigned lo = (unsigned)__double2loint(s[j]), hi = (unsigned)__double2hiint(s[j]);
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        s[j] = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x140>(s[j]);   // row mirror
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x141>(s[j]);   // half-row mirror
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x4E>(s[j]);    // lane ^ 2
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0xB1>(s[j]);    // lane ^ 1
+}
+
+__device__ __forceinline__ double lane_value(double x, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// More: steps of more than 256 pixels
+template <bool More>
+__global__ __launch_bounds__(kAdamThreads) void k_pose_adam(
+    prism_filter_state* __restrict__ S, CamC c, CamD cd, const float* __restrict__ obs_depth,
+    const float* __restrict__ obs_rgb, const float* __restrict__ a_depth, const float* __restrict__ a_rgb,
+    const uint8_t* __restrict__ a_mask, const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
+    WeightsC wt, const int32_t* __restrict__ pixels, AdamC ad) {
+    __shared__ Rel32 srel;
+    __shared__ double red[2][4][6], lpe[2][6];   // of even and odd steps
+    __shared__ double sRp[9], stp[3];
     __shared__ int skip;
     if (threadIdx.x == 0) {
         const prism_pose it = S->iter, pr = S->prior, an = S->anchor;
         skip = (S->flags & PRISM_FLAG_CHOL_FALLBACK) != 0;
         rel_of(&it, &an, srel);
-        quat_to_R9(pr.q, Rp);
-        for (int i = 0; i < 3; ++i) tp[i] = pr.t[i];
+        quat_to_R9(pr.q, sRp);
+        for (int i = 0; i < 3; ++i) stp[i] = pr.t[i];
     }
-    if (threadIdx.x < 36) Lp[threadIdx.x] = S->Lp[threadIdx.x];
     __syncthreads();
     if (skip) return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int npix = c.W * c.H;
-    double v2 = 0.0, b2k = 1.0;   // lanes 0..5 of wave 0: second moment of their component
-    // the observation at a thread's first sampled pixel does not depend on
-    // the pose: it is loaded one step ahead
-    auto fetch = [&](int step, int& p, float& D, float rgb[3]) {
-        p = -1;
-        if ((int)threadIdx.x < ad.n_pix) {
-            p = pixels[(long long)step * ad.n_pix + threadIdx.x];
-            if ((unsigned)p < (unsigned)npix) {
-                D = obs_depth[p];
-                rgb[0] = obs_rgb[3 * p];
-                rgb[1] = obs_rgb[3 * p + 1];
-                rgb[2] = obs_rgb[3 * p + 2];
-            } else {
-                p = -1;
-            }
-        }
+    Rel32 rel = srel;   // cur: the iterate (double R, t); prev: the anchor pose
+    double Lrow[6];     // prior wavefront: row `lane` of Lp
+#pragma unroll
+    for (int k = 0; k < 6; ++k) Lrow[k] = S->Lp[(lane < 6 ? lane : 0) * 6 + k];
+    double lr = ad.lr[lane < 6 ? lane : 0];
+    // arrived before the loop: a wait for them inside it would also wait for
+    // the loads a step requests ahead
+    asm volatile("" : "+v"(lr), "+v"(Lrow[0]), "+v"(Lrow[1]), "+v"(Lrow[2]), "+v"(Lrow[3]), "+v"(Lrow[4]), "+v"(Lrow[5]));
+    double v2 = 0.0, b2k = 1.0;   // second moment of component `lane`
+    // The thread's first sampled pixel of a step: its index is requested two
+    // steps ahead, its observation one step ahead (neither depends on the
+    // pose).  Even and odd steps hold theirs in registers of their own: handed
+    // on by copies, the values would be waited for when they are copied.
+    struct Sample {
+        int at;          // (row << 16 | column), or -1 for a pixel without rows
+        float D, rgb[3];
+    } sa, sb;
+    int ia = 0, ib = 0;
+    auto index_at = [&](int step, int j) {   // (a step or pixel past the last reads the last)
+        return pixels[(long long)min(step, ad.n_steps - 1) * ad.n_pix + min(j, ad.n_pix - 1)];
     };
-    int pn;
-    float Dn = 0.0f, cn[3] = {0.0f, 0.0f, 0.0f};
-    fetch(0, pn, Dn, cn);
-    for (int step = 0; step < ad.n_steps; ++step) {
-        double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        const int p0 = pn;
-        const float D0 = Dn, c0[3] = {cn[0], cn[1], cn[2]};
-        if (step + 1 < ad.n_steps) fetch(step + 1, pn, Dn, cn);
-        for (int j = threadIdx.x; j < ad.n_pix; j += 256) {
-            int p;
-            float D, orgb[3];
-            if (j == (int)threadIdx.x) {
-                p = p0;
-                D = D0;
-                orgb[0] = c0[0];
-                orgb[1] = c0[1];
-                orgb[2] = c0[2];
-                if (p < 0) continue;
-            } else {
-                p = pixels[(long long)step * ad.n_pix + j];
-                if ((unsigned)p >= (unsigned)npix) continue;
-                D = obs_depth[p];
-                orgb[0] = obs_rgb[3 * p];
-                orgb[1] = obs_rgb[3 * p + 1];
-                orgb[2] = obs_rgb[3 * p + 2];
-            }
-            float J[4][6];
-            double r[4];
-            int rm;
-            p2_pixel(c, cd, srel, p, D, orgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, wt, J, r, rm);
-            if (rm & 1)
+    auto observe = [&](int p, int j, Sample& o) {   // (no pixel: reads pixel 0)
+        const bool any = j < ad.n_pix && (unsigned)p < (unsigned)npix;
+        p = any ? p : 0;
+        o.D = obs_depth[p];
+        const float3u x = *reinterpret_cast<const float3u*>(obs_rgb + 3 * p);
+        o.rgb[0] = x[0];
+        o.rgb[1] = x[1];
+        o.rgb[2] = x[2];
+        int u, v;
+        pixel_uv(c.W, p, u, v);
+        o.at = any ? (v << 16) | u : -1;
+    };
+    if (wv < 4) {
+        ia = index_at(0, threadIdx.x);
+        ib = index_at(1, threadIdx.x);
+        observe(ia, threadIdx.x, sa);
+        // ahead of the prior wavefront, which shares a SIMD with one of these
+        __builtin_amdgcn_s_setprio(2);
+    }
+    // step `step`: the sample in `cur`; `inext`, the index of the next step's
+    // sample, becomes `next`, and the index of the step after it `iafter`
+    auto do_step = [&](int step, int buf, const Sample& cur, Sample& next, const int& inext, int& iafter) {
+        if (wv < 4) {
+            double g[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            if (cur.at >= 0)
+                p2_grad(c, cd, rel, cur.at & 0xffff, cur.at >> 16, cur.D, cur.rgb, a_depth, a_rgb, a_mask, a_normals,
+                        a_nmask, wt, g);
+            if constexpr (More)
+                for (int j = threadIdx.x + 256; j < ad.n_pix; j += 256) {
+                    Sample o;
+                    observe(index_at(step, j), j, o);
+                    if (o.at >= 0)
+                        p2_grad(c, cd, rel, o.at & 0xffff, o.at >> 16, o.D, o.rgb, a_depth, a_rgb, a_mask, a_normals,
+                                a_nmask, wt, g);
+                }
+            // requested only now: a wait for the anchor covers all earlier loads
+            __builtin_amdgcn_sched_barrier(0);
+            observe(inext, threadIdx.x, next);
+            iafter = index_at(step + 2, threadIdx.x);
+            double s[3];
+            wave_sum6(g, s);
+            if ((lane & 31) == 0)
 #pragma unroll
-                for (int m = 0; m < 6; ++m) g[m] += wt.w_depth * r[0] * (double)J[0][m];
-            if (rm & 2)
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch)
-#pragma unroll
-                    for (int m = 0; m < 6; ++m) g[m] += wt.w_rgb * r[1 + ch] * (double)J[1 + ch][m];
-        }
-        if (threadIdx.x == 255) {
+                for (int j = 0; j < 3; ++j) red[buf][wv][(lane >> 5) * 3 + j] = s[j];
+        } else {
             // prior term at the current iterate: e = (t - tp, Log(R Rp^T))
             double M[9], e[6];
             for (int i = 0; i < 3; ++i)
                 for (int k = 0; k < 3; ++k)
-                    M[i * 3 + k] = srel.cur.R[i][0] * Rp[k * 3] + srel.cur.R[i][1] * Rp[k * 3 + 1] +
-                                   srel.cur.R[i][2] * Rp[k * 3 + 2];
-            for (int i = 0; i < 3; ++i) e[i] = srel.cur.t[i] - tp[i];
+                    M[i * 3 + k] = rel.cur.R[i][0] * sRp[k * 3] + rel.cur.R[i][1] * sRp[k * 3 + 1] +
+                                   rel.cur.R[i][2] * sRp[k * 3 + 2];
+            for (int i = 0; i < 3; ++i) e[i] = rel.cur.t[i] - stp[i];
             so3_log(M, e + 3);
-            for (int i = 0; i < 6; ++i) {
-                double s = 0.0;
-                for (int k = 0; k < 6; ++k) s += Lp[i * 6 + k] * e[k];
-                lpe[i] = s;
-            }
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < 6; ++k) s += Lrow[k] * e[k];
+            if (lane < 6) lpe[buf][lane] = s;
         }
-#pragma unroll
-        for (int m = 0; m < 6; ++m)
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) g[m] += __shfl_xor(g[m], off, 64);
-        if (lane == 0)
-#pragma unroll
-            for (int m = 0; m < 6; ++m) red[wv][m] = g[m];
+        // formed ahead of the barrier
+        b2k *= ad.beta2;
+        const double corr = 1.0 / (1.0 - b2k);
         __syncthreads();
-        if (wv == 0) {
-            double di = 0.0;
-            if (lane < 6) {
-                const double gi = 2.0 * ad.scale * ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) +
-                                  lpe[lane];
-                b2k *= ad.beta2;
-                v2 = ad.beta2 * v2 + (1.0 - ad.beta2) * gi * gi;
-                const double vhat = v2 / (1.0 - b2k);
-                di = -ad.lr[lane] * gi / (sqrt(vhat) + ad.eps);
-            }
-            double d[6];
+        {
+#pragma clang fp contract(fast)
+            const int m6 = lane < 6 ? lane : 0;
+            const double gi = 2.0 * ad.scale * ((red[buf][0][m6] + red[buf][1][m6]) +
+                                                (red[buf][2][m6] + red[buf][3][m6])) + lpe[buf][m6];
+            v2 = ad.beta2 * v2 + (1.0 - ad.beta2) * gi * gi;
+            const double di = -lr * gi / (sqrt(v2 * corr) + ad.eps);
+            double d[6], E[9], R2[3][3], dd[3];
 #pragma unroll
-            for (int m = 0; m < 6; ++m) d[m] = __shfl(di, m, 64);
-            if (lane == 0) {
-                double E[9], R[9], R2[9];
-                so3_exp_step(d + 3, E);
-                for (int i = 0; i < 3; ++i)
-                    for (int k = 0; k < 3; ++k) R[i * 3 + k] = srel.cur.R[i][k];
-                mat3mul(E, R, R2);
-                const Pose64& Q = srel.prev;
-                double t[3], dd[3];
-                for (int i = 0; i < 3; ++i) {
-                    t[i] = srel.cur.t[i] + d[i];
-                    dd[i] = t[i] - Q.t[i];
-                }
+            for (int m = 0; m < 6; ++m) d[m] = lane_value(di, m);
+            so3_exp_step(d + 3, E);
+            const Pose64& Q = rel.prev;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    R2[i][k] = E[i * 3] * rel.cur.R[0][k] + E[i * 3 + 1] * rel.cur.R[1][k] + E[i * 3 + 2] * rel.cur.R[2][k];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                rel.cur.t[i] += d[i];
+                dd[i] = rel.cur.t[i] - Q.t[i];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) rel.cur.R[i][k] = R2[i][k];
+            }
+            if (wv < 4)   // the prior needs the iterate only
+#pragma unroll
                 for (int a = 0; a < 3; ++a) {
+#pragma unroll
                     for (int b = 0; b < 3; ++b)
-                        srel.R[a][b] = (float)((Q.R[0][a] * R2[b] + Q.R[1][a] * R2[3 + b]) + Q.R[2][a] * R2[6 + b]);
-                    srel.t[a] = (float)((Q.R[0][a] * dd[0] + Q.R[1][a] * dd[1]) + Q.R[2][a] * dd[2]);
+                        rel.R[a][b] = (float)(Q.R[0][a] * R2[0][b] + Q.R[1][a] * R2[1][b] + Q.R[2][a] * R2[2][b]);
+                    rel.t[a] = (float)(Q.R[0][a] * dd[0] + Q.R[1][a] * dd[1] + Q.R[2][a] * dd[2]);
                 }
-                for (int i = 0; i < 3; ++i) {
-                    srel.cur.t[i] = t[i];
-                    for (int k = 0; k < 3; ++k) srel.cur.R[i][k] = R2[i * 3 + k];
-                }
-            }
         }
-        __syncthreads();
+    };
+    for (int step = 0; step < ad.n_steps; step += 2) {
+        do_step(step, 0, sa, sb, ib, ia);
+        if (step + 1 == ad.n_steps) break;
+        do_step(step + 1, 1, sb, sa, ia, ib);
     }
     if (threadIdx.x == 0) {
         double R[9];
         for (int i = 0; i < 3; ++i)
-            for (int k = 0; k < 3; ++k) R[i * 3 + k] = srel.cur.R[i][k];
+            for (int k = 0; k < 3; ++k) R[i * 3 + k] = rel.cur.R[i][k];
         prism_pose it;
-        for (int i = 0; i < 3; ++i) it.t[i] = srel.cur.t[i];
+        for (int i = 0; i < 3; ++i) it.t[i] = rel.cur.t[i];
         R9_to_quat(R, it.q);
         S->iter = it;
     }
@@ -434,8 +610,8 @@ hipError_t launch_pose_adam(prism_filter_state* S, const CamC& c, const CamD& cd
                             const float* obs_rgb, const float* a_depth, const float* a_rgb, const uint8_t* a_mask,
                             const float* a_normals, const uint8_t* a_nmask, const WeightsC& w, const int32_t* pixels,
                             const AdamC& ad, hipStream_t st) {
-    k_pose_adam<<<1, 256, 0, st>>>(S, c, cd, obs_depth, obs_rgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, w, pixels,
-                                   ad);
+    auto* k = ad.n_pix > 256 ? k_pose_adam<true> : k_pose_adam<false>;
+    k<<<1, kAdamThreads, 0, st>>>(S, c, cd, obs_depth, obs_rgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, w, pixels, ad);
     return hipGetLastError();
 }
 

@@ -835,6 +835,38 @@ def test_filter_adam_matches_oracle():
         assert abs(int(s.n_updated) - of.s.last["n_updated"]) <= max(10, 1e-4 * of.s.last["n_updated"])
 
 
+@pytest.mark.parametrize("n_pixels,n_steps,lr_r", [(1, 3, 0.00036), (64, 1, 0.00036), (255, 4, 0.00036),
+                                                   (256, 5, 0.00036), (257, 4, 0.00036), (700, 3, 0.02)])
+def test_adam_sample_counts_and_step_sizes(n_pixels, n_steps, lr_r):
+    """The optimiser at the edges of its work split (a lane's one sample, the
+    256 of a step, more), odd and single step counts, and steps of more than
+    0.01 rad, against the oracle: the pose bar of the filter tests."""
+    banner(f"adam {n_pixels} pixels x {n_steps} steps, lr_r {lr_r}")
+    c = synth.trajectory_case(seed=4, n=64, width=75, height=61, n_samples=32, n_frames=2)
+    tr = c["traj"]
+    f = P().Filter(grid_of(c["scene"], 0), cam_of(c["cam"]), P().FilterParams(objective=0))
+    f.map.init()
+    x0 = np.concatenate([tr.t[0], tr.q[0], tr.v[0], tr.w[0]])
+    P0 = np.diag([1e-6] * 6 + [1e-4] * 6)
+    f.reset(x0, P0)
+    mean = np.zeros((4, 64, 64, 64)); mean[0] = np.float32(-0.001)
+    of = orc.Filter(orc.grid_from_scene(c["scene"]), orc.cam_from(c["cam"]), orc.Params(objective="p2"),
+                    dict(t=tr.t[0], q=tr.q[0], v=tr.v[0], w=tr.w[0]), P0, mean, np.full_like(mean, 1e4))
+    ap = P().AdamParams.make(n_steps=n_steps, n_pixels=n_pixels, lr_r=lr_r)
+    for i in range(2):
+        pix = synth.sample_pixels(20 + i, n_steps, n_pixels, c["cam"].height, c["cam"].width)
+        pix[-1, -1] = -7 if n_pixels > 1 else pix[-1, -1]
+        u = tr.u[i - 1] if i else None
+        f.step_adam(t(c["depth"][i]), t(c["rgb"][i]), t(u, torch.float64) if i else None, ap, t(pix, torch.int32))
+        of.step(c["depth"][i].astype(np.float64), c["rgb"][i].astype(np.float64), u,
+                adam=dict(pixels=pix, lr_t=ap.lr_t, lr_r=ap.lr_r, beta2=ap.beta2, eps=ap.eps))
+    s = f.state()
+    dt_ = np.linalg.norm(np.array(s.pose.t) - of.s.t)
+    dr = rot_angle(np.array(s.pose.q), of.s.q)
+    print(f"|dt| {dt_:.3e} dR {dr:.3e}", flush=True)
+    assert dt_ <= 1e-5 and dr <= 1e-5
+
+
 def test_adam_rejects_p1_and_bad_samples():
     banner("adam argument checks")
     c = synth.trajectory_case(seed=2, n=64, width=80, height=60, n_samples=32, n_frames=1)
