@@ -687,7 +687,7 @@ prism_status prism_render_jacobian(const prism_grid* grid, const void* map, cons
     HIP_TRY(launch_render_jac(grid_cm(grid, map), c, grid_d(grid), cam_d(cam), grid->dtype, map,
                               skip_table(grid, cam, map), poses, n_frames, obs_depth, obs_rgb, weights_c(w),
                               depth, rgb, mask, J, resid, rowmask, part, stream));
-    HIP_TRY(launch_finalize(part, render_blocks(c), n_frames, PRISM_NEQ, neq, PRISM_NEQ, stream));
+    HIP_TRY(launch_finalize(part, render_blocks(c), n_frames, neq, stream));
     return PRISM_OK;
 }
 
@@ -755,7 +755,7 @@ prism_status prism_render_jacobian_noalloc(const prism_grid* grid, const void* m
     HIP_TRY(launch_render_jac(grid_cm(grid, map), c, grid_d(grid), cam_d(cam), grid->dtype, map,
                               skip_table(grid, cam, map), poses, n_frames, obs_depth, obs_rgb, weights_c(w),
                               depth, rgb, mask, J, resid, rowmask, (double*)part, stream));
-    HIP_TRY(launch_finalize((const double*)part, render_blocks(c), n_frames, PRISM_NEQ, neq, PRISM_NEQ, stream));
+    HIP_TRY(launch_finalize((const double*)part, render_blocks(c), n_frames, neq, stream));
     return PRISM_OK;
 }
 
@@ -779,7 +779,7 @@ prism_status prism_track_p2(const prism_camera* cam, const prism_pose* pose, con
     double* part = (double*)workspace;
     HIP_TRY(launch_track_p2(c, cam_d(cam), pose, pose_prev, obs_depth, obs_rgb, anchor_depth, anchor_rgb, anchor_mask,
                             anchor_normals, anchor_nmask, weights_c(w), J, resid, rowmask, part, nullptr, stream));
-    HIP_TRY(launch_finalize(part, track_blocks(c), 1, PRISM_NEQ, neq, PRISM_NEQ, stream));
+    HIP_TRY(launch_finalize(part, track_blocks(c), 1, neq, stream));
     return PRISM_OK;
 }
 
@@ -804,7 +804,7 @@ prism_status prism_render_vjp(const prism_grid* grid, const void* map, const pri
     double* part = (double*)workspace;
     HIP_TRY(launch_render_vjp(grid_c(grid), c, grid_d(grid), cam_d(cam), (const float*)map, poses, n_frames, hit_k, g_depth, g_rgb, grad_mean,
                               part, stream));
-    HIP_TRY(launch_finalize(part, vjp_blocks(c), n_frames, 6, grad_pose, 6, stream));
+    HIP_TRY(launch_finalize6(part, vjp_blocks(c), n_frames, grad_pose, stream));
     return PRISM_OK;
 }
 
@@ -890,15 +890,13 @@ prism_status prism_map_gd(const prism_grid* grid, void* map, const prism_camera*
     WeightsC wc = weights_c(w);
     MapAux aux = map_aux(grid, map);
     const unsigned* bits = skip_table(grid, cam, map);
-    HIP_TRY(launch_gd_clear(marks, L.words, stream));
-    HIP_TRY(launch_gd_clear(saved, L.words, stream));
-    HIP_TRY(launch_gd_clear((unsigned*)list, 1, stream));
+    // the marks, the saved bits and the list's count, which lie one after another
+    HIP_TRY(launch_gd_clear(marks, (int)((L.list - L.marks) / 4) + 1, stream));
     for (int it = 0; it < n_iters; ++it) {
         HIP_TRY(launch_gd_grad(g, c, gd, cd, (const float*)map, bits, pose, obs_depth, obs_rgb, wc, grad, marks, list,
                                pd, stream));
-        HIP_TRY(launch_gd_update(g, (float*)map, aux, save, grad, list, saved, lr_occ, lr_rgb, pp, stream));
-        if (cost)
-            HIP_TRY(launch_gd_cost(pd, render_blocks(c), pp, gd_update_groups(g), cost + it, stream));
+        HIP_TRY(launch_gd_update(g, (float*)map, aux, save, grad, list, saved, lr_occ, lr_rgb, pp, pd,
+                                 render_blocks(c), cost ? cost + it : nullptr, stream));
     }
     return PRISM_OK;
 }

@@ -126,8 +126,9 @@ hipError_t launch_track_p2(const CamC& c, const CamD& cd, const prism_pose* pose
                            const float* a_rgb, const uint8_t* a_mask, const float* a_normals,
                            const uint8_t* a_nmask, const WeightsC& w, float* J, float* resid,
                            uint8_t* rowmask, double* partials, const Rel32* rel, hipStream_t st);
-hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, int nvals, double* out,
-                           int stride, hipStream_t st);
+// per-frame sums of the partial rows: 29 values, or the adjoint's 6 pose sums
+hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st);
+hipError_t launch_finalize6(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st);
 
 hipError_t launch_map_init(const GridC& g, int dtype, void* map, float occ0, float rgb0, float var0,
                            const MapAux& aux, hipStream_t st);
@@ -149,15 +150,16 @@ int map_update_groups(const GridC& g);
 int map_update_groups_batch(const GridC& g);
 
 // descent mapping (gradient pass, step on marked bricks, cost total)
-// list: [0] number of bricks, then the bricks, in the order first touched
+// list: [0] number of bricks, then the bricks, in the order first touched;
+// cost (nullable): the objective before the step, from the nd data partials
+// pd and the step's previous-belief partials
 hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const CamD& cd, const float* map,
                           const unsigned* bits, const prism_pose* pose, const float* obs_depth, const float* obs_rgb,
                           const WeightsC& w, double* grad, unsigned* marks, int* list, double* partials,
                           hipStream_t st);
 hipError_t launch_gd_update(const GridC& g, float* map, const MapAux& aux, float* save, double* grad,
                             const int* list, unsigned* saved, double lr_occ, double lr_rgb, double* partials,
-                            hipStream_t st);
-hipError_t launch_gd_cost(const double* pd, int nd, const double* pp, int np, double* cost, hipStream_t st);
+                            const double* pd, int nd, double* cost, hipStream_t st);
 hipError_t launch_gd_clear(unsigned* words, int n, hipStream_t st);
 int gd_update_groups(const GridC& g);
 

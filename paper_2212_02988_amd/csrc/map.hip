@@ -811,10 +811,18 @@ __global__ __launch_bounds__(256) void k_gd_update(GridC g, float* __restrict__ 
     if (threadIdx.x == 0) partials[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
 }
 
-// cost[0] = sum of the data partials + sum of the previous-belief partials
-__global__ __launch_bounds__(256) void k_gd_cost(const double* __restrict__ pd, int nd,
-                                                 const double* __restrict__ pp, int np, double* __restrict__ cost) {
+// The dilated bits after a descent step, with workgroup 0 also totalling the
+// objective before the step: cost[0] = sum of the data partials + sum of the
+// previous-belief partials, by the whole workgroup in a fixed order.
+__global__ __launch_bounds__(256) void k_dilate_bits_cost(int nb, unsigned* __restrict__ bits,
+                                                          const double* __restrict__ pd, int nd,
+                                                          const double* __restrict__ pp, int np,
+                                                          double* __restrict__ cost) {
     __shared__ double red[256];
+    if (blockIdx.x > 0) {
+        dilate_block(blockIdx.x - 1, nb, bits);
+        return;
+    }
     double a = 0.0;
     for (int i = threadIdx.x; i < nd; i += 256) a += pd[i];
     for (int i = threadIdx.x; i < np; i += 256) a += pp[i];
@@ -844,16 +852,14 @@ hipError_t launch_gd_clear(unsigned* words, int n, hipStream_t st) {
 
 hipError_t launch_gd_update(const GridC& g, float* map, const MapAux& aux, float* save, double* grad,
                             const int* list, unsigned* saved, double lr_occ, double lr_rgb, double* partials,
-                            hipStream_t st) {
+                            const double* pd, int nd, double* cost, hipStream_t st) {
     k_gd_update<<<gd_update_groups(g), 256, 0, st>>>(g, map, aux, save, grad, list, saved, lr_occ, lr_rgb,
                                                      partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_dilate(g, aux, st);
-}
-
-hipError_t launch_gd_cost(const double* pd, int nd, const double* pp, int np, double* cost, hipStream_t st) {
-    k_gd_cost<<<1, 256, 0, st>>>(pd, nd, pp, np, cost);
+    if (!cost) return launch_dilate(g, aux, st);
+    k_dilate_bits_cost<<<(unsigned)((free_words(g.nb) + 255) / 256) + 1, 256, 0, st>>>(g.nb, aux.bits, pd, nd, partials,
+                                                                                      gd_update_groups(g), cost);
     return hipGetLastError();
 }
 

@@ -17,6 +17,8 @@
 // The adjoint takes four lanes per ray as well (8x8 pixels per workgroup):
 // from the given hit index it recomputes the two samples, nothing to march,
 // and lane s scatters the gradient of plane s.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -753,52 +755,271 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 }
 
 // ---------------------------------------------------------------------------
+// scattering a tile's gradient into the map
+// ---------------------------------------------------------------------------
+// The 16 rays of a wavefront's 4x4 pixels reach some dozens of distinct voxels
+// through 256 corners per plane, so a wavefront first sums its contributions
+// in LDS of its own and then issues one global atomic per distinct (plane,
+// voxel).  Rays that see one surface reach a small box of voxels: the sums
+// live in a window over that box, addressed directly, and go out in window
+// order, where neighbouring lanes hold neighbouring voxels of a brick row and
+// their atomics share cache lines.  (256 voxels hold 99 % of the boxes of a
+// 320x240 view of a 256^3 map of 2.5 cm voxels.)  Rays whose box is larger see
+// surfaces far apart, or voxels that are small beside their pixels, and share
+// few voxels: they add to global memory directly.
+//
+// LDS float atomics would bound a scatter by corners (170 clocks per
+// instruction measured, whether or not lanes meet in an address), so the
+// window is summed with plain reads and writes, which needs the addresses of
+// one instruction to differ.  A cell's eight corners lie in the eight parity
+// classes of (x, y, z); in turn q ray r takes its corner of class q ^ r, so
+// eight consecutive rays always hold eight different classes, hence voxels;
+// the two eights of a wavefront have a copy of the window each or take turns,
+// the four lanes of a ray have a plane each, and no other wavefront shares
+// the window.  Measured at 256^3, 320x240 (hash tables per tile before): the
+// adjoint of 8 frames 399 -> 113 us (67 without any scatter), the descent
+// gradient 72 -> 40 us (23).
+constexpr int kWin = 256;   // voxels per plane; a box of as many spans fewer than 64 bricks
+
+template <typename V, int Copies>
+struct Scatter {
+    V win[4][Copies][kWin + 8];   // planes and copies shifted in the banks
+};
+
+// the wavefront's box of vol = dx dy dz voxels from (x0, y0, z0); vol 0: no
+// lane has a corner, -1: larger than a window
+struct Window {
+    int x0, y0, z0, dx, dy, dz, vol;
+};
+
+// a workgroup's: its four wavefronts' windows
+template <typename V, int Copies>
+struct TileScatter {
+    Scatter<V, Copies> wave[4];
+    Window at[4];
+    int mark[256];   // bricks of a box that goes out (of each window's 64, when they go out one by one)
+};
+
+// LDS operations of a wavefront take effect in program order; this keeps the
+// compiler from moving them across each other (no instruction)
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// pixels of a scattering wavefront: 4x4, four wavefronts per 8x8 tile
+__device__ __forceinline__ void scatter_pixel(const CamC& c, int blk, int& u, int& v, int& s) {
+    const int tiles_x = (c.W + 7) >> 3, t = threadIdx.x, r = (t >> 2) & 15, wv = t >> 6;
+    s = t & 3;
+    u = ((blk % tiles_x) << 3) + ((wv & 1) << 2) + (r & 3);
+    v = ((blk / tiles_x) << 3) + ((wv >> 1) << 2) + (r >> 2);
+}
+
+// every lane's two cells (live: the lane's ray contributes) -> the window,
+// cleared; the whole wavefront
+template <typename V, int Copies>
+__device__ __forceinline__ Window scatter_window(const GridC& g, Scatter<V, Copies>& S, bool live, const Cell& c0,
+                                                 const Cell& c1) {
+    int lo[3], hi[3];
+    bool any = live;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = max(min(c0.i[a], c1.i[a]), 0);
+        hi[a] = min(max(c0.i[a], c1.i[a]) + 1, g.n - 1);
+        any &= lo[a] <= hi[a];
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        int l = any ? lo[a] : INT_MAX, h = any ? hi[a] : -1;
+        // the four lanes of a ray agree: quads, then rows, then the wavefront
+        l = min(l, __builtin_amdgcn_update_dpp(l, l, 0x141, 0xF, 0xF, false));
+        h = max(h, __builtin_amdgcn_update_dpp(h, h, 0x141, 0xF, 0xF, false));
+        l = min(l, __builtin_amdgcn_update_dpp(l, l, 0x140, 0xF, 0xF, false));
+        h = max(h, __builtin_amdgcn_update_dpp(h, h, 0x140, 0xF, 0xF, false));
+        l = min(l, __shfl_xor(l, 16, 64));
+        h = max(h, __shfl_xor(h, 16, 64));
+        lo[a] = __builtin_amdgcn_readfirstlane(min(l, __shfl_xor(l, 32, 64)));
+        hi[a] = __builtin_amdgcn_readfirstlane(max(h, __shfl_xor(h, 32, 64)));
+    }
+    Window w{lo[0], lo[1], lo[2], 0, 0, 0, 0};
+    if (hi[0] < 0) return w;
+    w.dx = hi[0] - lo[0] + 1;
+    w.dy = hi[1] - lo[1] + 1;
+    w.dz = hi[2] - lo[2] + 1;
+    w.vol = w.dx * w.dy * w.dz;   // at most 2^30
+    if (w.vol > kWin) {
+        w.vol = -1;
+        return w;
+    }
+    for (int e = threadIdx.x & 63; e < w.vol; e += 64)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int k = 0; k < Copies; ++k) S.win[p][k][e] = V(0);
+    wave_lds_order();
+    return w;
+}
+
+// no brick marks wanted
+struct NoMarks {
+    __device__ void operator()(int) const {}
+};
+
+__device__ __forceinline__ void grad_out(float* p, float v) { atomicAdd(p, v); }
+__device__ __forceinline__ void grad_out(double* p, double v) { unsafeAtomicAdd(p, v); }
+
+// coef * (trilinear weight) into plane s at the in-grid corners of the cell
+// (add: this lane does); touched(b): a brick that was added to in global
+// memory.  The whole wavefront.
+template <typename V, int Copies, typename Touched>
+__device__ __forceinline__ void scatter_cell(const GridC& g, Scatter<V, Copies>& S, const Window& w, int s,
+                                             const Cell& cl, const float wt[3], V coef, bool add,
+                                             V* __restrict__ grad, const Touched& touched) {
+    const int r = (threadIdx.x >> 2) & 15;   // ray of the wavefront
+    int c[3][2];
+    V hat[3][2];
+    bool ok[3][2];
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int far = ((cl.i[a] ^ (r >> a)) & 1) ^ d;   // corner of the axis's parity class r ^ d
+            c[a][d] = cl.i[a] + far;
+            hat[a][d] = (V)(far ? wt[a] : 1.0f - wt[a]);
+            ok[a][d] = (unsigned)c[a][d] < (unsigned)g.n;
+        }
+    if (w.vol <= 0) {
+        if (!add || w.vol == 0) return;
+#pragma unroll 1
+        for (int q = 0; q < 8; ++q) {
+            const bool fx = q & 1, fy = q & 2, fz = q & 4;
+            if (!((fx ? ok[0][1] : ok[0][0]) && (fy ? ok[1][1] : ok[1][0]) && (fz ? ok[2][1] : ok[2][0]))) continue;
+            const int id = (int)vidx(g, fx ? c[0][1] : c[0][0], fy ? c[1][1] : c[1][0], fz ? c[2][1] : c[2][0]);
+            grad_out(grad + (long long)s * g.nvox + id,
+                     coef * ((fx ? hat[0][1] : hat[0][0]) * (fy ? hat[1][1] : hat[1][0]) * (fz ? hat[2][1] : hat[2][0])));
+            touched(id >> 9);
+        }
+        return;
+    }
+    int off[3][2];
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        off[0][d] = c[0][d] - w.x0;
+        off[1][d] = (c[1][d] - w.y0) * w.dx;
+        off[2][d] = (c[2][d] - w.z0) * w.dx * w.dy;
+    }
+    V* const win = &S.win[s][Copies == 2 ? r >> 3 : 0][0];
+#pragma unroll
+    for (int turn = 0; turn < 2 / Copies; ++turn) {
+        if (add && (Copies == 2 || (r >> 3) == turn)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int dx = q & 1, dy = (q >> 1) & 1, dz = q >> 2;
+                if (ok[0][dx] && ok[1][dy] && ok[2][dz])
+                    win[off[0][dx] + off[1][dy] + off[2][dz]] += coef * (hat[0][dx] * hat[1][dy] * hat[2][dz]);
+                wave_lds_order();
+            }
+        }
+        wave_lds_order();
+    }
+}
+
+// the sums of voxel (x, y, z) in window w of wavefront wv, added to sum
+template <typename V, int Copies>
+__device__ __forceinline__ void window_add(const TileScatter<V, Copies>& T, int wv, const Window& w, int x, int y,
+                                           int z, V sum[4]) {
+    x -= w.x0;
+    y -= w.y0;
+    z -= w.z0;
+    if (w.vol <= 0 || (unsigned)x >= (unsigned)w.dx || (unsigned)y >= (unsigned)w.dy || (unsigned)z >= (unsigned)w.dz)
+        return;
+    const int e = (z * w.dy + y) * w.dx + x;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int k = 0; k < Copies; ++k) sum[p] += T.wave[wv].win[p][k][e];
+}
+
+// The tile's sums to global memory, one atomic per (plane, voxel) that is not
+// zero; touched(b): each brick that received something.  Global atomics bound
+// the scatter once the window sums are cheap, so the four windows are summed
+// on the way out (a voxel on their borders goes out once), over the box of all
+// four in brick order: lanes in eights hold a brick row's voxels.  Windows far
+// apart (a box beyond kTileBox) go out one by one.  The whole workgroup.
+constexpr int kTileBox = 2048;   // spans at most 256 bricks
+
+template <typename V, int Copies, typename Touched>
+__device__ __forceinline__ void scatter_flush(const GridC& g, TileScatter<V, Copies>& T, const Window& mine,
+                                              V* __restrict__ grad, const Touched& touched) {
+    const int wv = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) T.at[wv] = mine;
+    __syncthreads();
+    Window w[4];
+    int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {-1, -1, -1};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        w[k] = T.at[k];
+        if (w[k].vol <= 0) continue;
+        lo[0] = min(lo[0], w[k].x0);
+        lo[1] = min(lo[1], w[k].y0);
+        lo[2] = min(lo[2], w[k].z0);
+        hi[0] = max(hi[0], w[k].x0 + w[k].dx - 1);
+        hi[1] = max(hi[1], w[k].y0 + w[k].dy - 1);
+        hi[2] = max(hi[2], w[k].z0 + w[k].dz - 1);
+    }
+    if (hi[0] < 0) return;
+    auto box = [&](int first, int step, const int lo[3], const int hi[3], int k0, int k1, int* mark, auto&& order) {
+        const int gx0 = lo[0] >> 3, dy = hi[1] - lo[1] + 1, dz = hi[2] - lo[2] + 1;
+        const int ngx = (hi[0] >> 3) - gx0 + 1, vol = ngx * 8 * dy * dz;
+        constexpr bool marks = !std::is_same<Touched, NoMarks>::value;
+        const int by0 = lo[1] >> 3, nby = (hi[1] >> 3) - by0 + 1, bz0 = lo[2] >> 3, nbz = (hi[2] >> 3) - bz0 + 1;
+        if constexpr (marks) {
+            for (int e = first; e < ngx * nby * nbz; e += step) mark[e] = 0;
+            order();
+        }
+        // quotients of small integers by a reciprocal: (r + 1/2) / d is at
+        // least 1/(2d) from an integer
+        const float iy = __builtin_amdgcn_rcpf((float)dy), iz = __builtin_amdgcn_rcpf((float)dz);
+        for (int e = first; e < vol; e += step) {
+            const int r = e >> 3, ry = (int)(((float)r + 0.5f) * iy), gx = (int)(((float)ry + 0.5f) * iz);
+            const int x = ((gx0 + gx) << 3) | (e & 7), y = lo[1] + r - ry * dy, z = lo[2] + ry - gx * dz;
+            V sum[4] = {V(0), V(0), V(0), V(0)};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k >= k0 && k < k1) window_add(T, k, w[k], x, y, z, sum);
+            const long long id = vidx(g, x, y, z);
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                if (sum[p] != V(0)) {
+                    grad_out(grad + (long long)p * g.nvox + id, sum[p]);
+                    if constexpr (marks) mark[(((z >> 3) - bz0) * nby + (y >> 3) - by0) * ngx + gx] = 1;
+                }
+        }
+        // once per box: a look at a brick's mark waits for the atomics before it
+        if constexpr (marks) {
+            order();
+            for (int e = first; e < ngx * nby * nbz; e += step)
+                if (mark[e]) touched(((bz0 + e / (ngx * nby)) * g.nb + by0 + (e / ngx) % nby) * g.nb + gx0 + e % ngx);
+        }
+    };
+    const long long vol = ((hi[0] >> 3) - (lo[0] >> 3) + 1) * 8LL * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
+    if (vol <= kTileBox) {
+        box((int)threadIdx.x, 256, lo, hi, 0, 4, T.mark, [] { __syncthreads(); });
+    } else if (mine.vol > 0) {
+        const int l[3] = {mine.x0, mine.y0, mine.z0};
+        const int h[3] = {mine.x0 + mine.dx - 1, mine.y0 + mine.dy - 1, mine.z0 + mine.dz - 1};
+        box((int)(threadIdx.x & 63), 64, l, h, wv, wv + 1, T.mark + 64 * wv, [] { wave_lds_order(); });
+    }
+}
+
+// ---------------------------------------------------------------------------
 // adjoint of render w.r.t. map means (atomic scatter) and pose
 // ---------------------------------------------------------------------------
 // Four lanes per ray, as in the render: lane s recomputes plane s of the
 // forward pass at the ray's first crossing (the plane's corners at the two
 // cells, the double-precision shading, its row of the Jacobian) and scatters
-// its share of the upstream gradient to the plane's 16 corners.  The 64 rays
-// of an 8x8 tile reach a few hundred distinct voxels through 1024 corners per
-// plane: the contributions are summed in an LDS table per plane (open
-// addressing on the voxel index), and each distinct (plane, voxel) then costs
-// one global atomic.  A corner that finds no slot within a few probes is
-// added to global memory directly.
-constexpr int kVjpSlots = 512;   // per plane (power of two)
-constexpr int kVjpProbes = 8;
-
-struct VjpAgg {
-    int key[4][kVjpSlots];       // voxel index, -1 = empty
-    float val[4][kVjpSlots];
-};
-
-__device__ __forceinline__ void vjp_add(VjpAgg& A, int s, int id, float val, float* __restrict__ grad_mean,
-                                        long long nvox) {
-    const unsigned h = ((unsigned)id * 2654435761u) >> (32 - 9);
-#pragma unroll 1
-    for (int p = 0; p < kVjpProbes; ++p) {
-        const int slot = (int)((h + p) & (kVjpSlots - 1));
-        const int prev = atomicCAS(&A.key[s][slot], -1, id);
-        if (prev == -1 || prev == id) {
-            __hip_atomic_fetch_add(&A.val[s][slot], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return;
-        }
-    }
-    atomicAdd(grad_mean + (long long)s * nvox + id, val);
-}
-
-// coef * (trilinear weight) into plane s at the in-grid corners of the cell
-__device__ __forceinline__ void vjp_cell(const GridC& g, VjpAgg& A, int s, const Cell& cl, const float w[3],
-                                         float coef, float* __restrict__ grad_mean) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int dx = q & 1, dy = (q >> 1) & 1, dz = q >> 2;
-        const int i = cl.i[0] + dx, j = cl.i[1] + dy, k = cl.i[2] + dz;
-        if ((unsigned)i >= (unsigned)g.n || (unsigned)j >= (unsigned)g.n || (unsigned)k >= (unsigned)g.n) continue;
-        const float hw = (dx ? w[0] : 1.0f - w[0]) * (dy ? w[1] : 1.0f - w[1]) * (dz ? w[2] : 1.0f - w[2]);
-        vjp_add(A, s, (int)vidx(g, i, j, k), coef * hw, grad_mean, g.nvox);
-    }
-}
+// its share of the upstream gradient to the plane's 16 corners.
+using VjpScatter = TileScatter<float, 2>;    // 33 KB: four workgroups per CU, as many as the registers allow
 
 // sum over the quad in single precision (every lane ends with (x0 + x1) + (x2 + x3))
 __device__ __forceinline__ float quad_sumf(float x) {
@@ -807,6 +1028,7 @@ __device__ __forceinline__ float quad_sumf(float x) {
     return x;
 }
 
+// partials: six pose sums per workgroup
 __global__ __launch_bounds__(256) void k_render_vjp(GridC g, CamC c, GridD gd, CamD cd, const float* __restrict__ map,
                                                     const prism_pose* __restrict__ poses,
                                                     const int32_t* __restrict__ hit_k,
@@ -815,18 +1037,15 @@ __global__ __launch_bounds__(256) void k_render_vjp(GridC g, CamC c, GridD gd, C
                                                     float* __restrict__ grad_mean,
                                                     double* __restrict__ partials) {
     __shared__ BlockPose sp;
-    __shared__ double lds[kRedLds];
-    __shared__ VjpAgg A;
-    for (int e = threadIdx.x; e < 4 * kVjpSlots; e += 256) {
-        (&A.key[0][0])[e] = -1;
-        (&A.val[0][0])[e] = 0.0f;
-    }
+    __shared__ double wsum[4][6];
+    __shared__ VjpScatter T;
     const BlockPose& P = block_pose(poses + blockIdx.y, &sp);   // synchronises the workgroup
     int u, v, s;
-    quad_pixel(c, blockIdx.x, u, v, s);
-    double acc[PRISM_NEQ];
-#pragma unroll
-    for (int q = 0; q < PRISM_NEQ; ++q) acc[q] = 0.0;
+    scatter_pixel(c, blockIdx.x, u, v, s);
+    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    Cell c0{}, c1{};
+    float w0[3] = {0.0f, 0.0f, 0.0f}, w1[3] = {0.0f, 0.0f, 0.0f}, k0 = 0.0f, k1 = 0.0f;
+    bool live = false;
     if (u < c.W && v < c.H) {
         const long long pix = (long long)blockIdx.y * c.W * c.H + (long long)v * c.W + u;
         const int k = hit_k[pix];
@@ -834,7 +1053,8 @@ __global__ __launch_bounds__(256) void k_render_vjp(GridC g, CamC c, GridD gd, C
             float dir[3];
             ray_dir32(c, P.f, u, v, dir);
             const RayCoef rc = ray_coef(g, c, P.f, dir);
-            const Cell c0 = sample_cell(rc, k - 1), c1 = sample_cell(rc, k);
+            c0 = sample_cell(rc, k - 1);
+            c1 = sample_cell(rc, k);
             const QuadShade q = shade_quad<float, false>(g, gd, cd, P.d, u, v, map, c0, c1, k, s);
             // the forward pass's crossing test on lane 0's occupancy corners
             const int crossing = trilerp(q.cv1, c1.w) > c.tau && !(trilerp(q.cv0, c0.w) > c.tau) ? 1 : 0;
@@ -850,40 +1070,37 @@ __global__ __launch_bounds__(256) void k_render_vjp(GridC g, CamC c, GridD gd, C
                 const float ga = quad_sumf(gs * (s == 0 ? q.d1 - q.d0 : (float)q.v1 - (float)q.v0));
                 const float al = (float)q.alpha;
                 const float inv_den = (float)(1.0 / (q.f1 - q.f0));
-                const float k0 = s == 0 ? -ga * (1.0f - al) * inv_den : gs * (1.0f - al);
-                const float k1 = s == 0 ? -ga * al * inv_den : gs * al;
-                vjp_cell(g, A, s, c0, q.w0, k0, grad_mean);
-                vjp_cell(g, A, s, c1, q.w1, k1, grad_mean);
+                k0 = s == 0 ? -ga * (1.0f - al) * inv_den : gs * (1.0f - al);
+                k1 = s == 0 ? -ga * al * inv_den : gs * al;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    w0[a] = q.w0[a];
+                    w1[a] = q.w1[a];
+                }
+                live = true;
             }
         }
     }
-    block_reduce29(acc, lds, partials + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * PRISM_NEQ);
+    double sum[3];
+    wave_sum6(acc, sum);
+    if ((threadIdx.x & 31) == 0)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) wsum[threadIdx.x >> 6][((threadIdx.x >> 5) & 1) * 3 + j] = sum[j];
     __syncthreads();
-    // one global atomic per distinct (plane, voxel) of the tile
-    for (int e = threadIdx.x; e < 4 * kVjpSlots; e += 256) {
-        const int key = (&A.key[0][0])[e];
-        if (key < 0) continue;
-        atomicAdd(grad_mean + (long long)(e / kVjpSlots) * g.nvox + key, (&A.val[0][0])[e]);
-    }
+    if (threadIdx.x < 6)
+        partials[((long long)blockIdx.y * gridDim.x + blockIdx.x) * 6 + threadIdx.x] =
+            (wsum[0][threadIdx.x] + wsum[1][threadIdx.x]) + (wsum[2][threadIdx.x] + wsum[3][threadIdx.x]);
+    Scatter<float, 2>& A = T.wave[threadIdx.x >> 6];
+    const Window w = scatter_window(g, A, live, c0, c1);
+    const NoMarks touched;
+    scatter_cell(g, A, w, s, c0, w0, k0, live, grad_mean, touched);
+    scatter_cell(g, A, w, s, c1, w1, k1, live, grad_mean, touched);
+    scatter_flush(g, T, w, grad_mean, touched);
 }
 
 // ---------------------------------------------------------------------------
 // gradient of the map-filter objective w.r.t. the map means (descent mapping)
 // ---------------------------------------------------------------------------
-// Per-workgroup accumulation table: the rays of an 8x8 tile touch a few
-// hundred distinct (plane, voxel) pairs through thousands of trilinear
-// corner contributions, so the contributions are summed in LDS first and each
-// distinct pair costs one global atomic.  Open addressing on the voxel index
-// (brick order) per plane; a contribution that finds no slot within a few
-// probes goes straight to global memory.
-constexpr int kAggSlots = 512;   // per plane (power of two)
-constexpr int kAggProbes = 8;
-
-struct GdAgg {
-    int key[4][kAggSlots];      // voxel index, -1 = empty
-    double val[4][kAggSlots];
-};
-
 // Sets the brick's bit; the caller that flips it appends the brick to the
 // list of bricks the step has to visit.
 __device__ __forceinline__ void mark_brick(unsigned* __restrict__ marks, int* __restrict__ list, int b) {
@@ -896,37 +1113,7 @@ __device__ __forceinline__ void mark_brick(unsigned* __restrict__ marks, int* __
     }
 }
 
-__device__ __forceinline__ void agg_add(GdAgg& A, int s, long long id, double val, double* __restrict__ grad,
-                                        long long nvox, unsigned* __restrict__ marks, int* __restrict__ list) {
-    const int key = (int)id;
-    unsigned h = ((unsigned)key * 2654435761u) >> (32 - 9);
-#pragma unroll 1
-    for (int p = 0; p < kAggProbes; ++p) {
-        const int slot = (int)((h + p) & (kAggSlots - 1));
-        const int prev = atomicCAS(&A.key[s][slot], -1, key);
-        if (prev == -1 || prev == key) {
-            __hip_atomic_fetch_add(&A.val[s][slot], val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            return;
-        }
-    }
-    unsafeAtomicAdd(grad + (long long)s * nvox + id, val);
-    mark_brick(marks, list, (int)(id >> 9));
-}
-
-// coef * (trilinear weight) for the in-grid corners of the cell
-__device__ __forceinline__ void agg_cell(const GridC& g, GdAgg& A, int s, const Cell& cl, const float w[3],
-                                         double coef, double* __restrict__ grad, unsigned* __restrict__ marks,
-                                         int* __restrict__ list) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int dx = q & 1, dy = (q >> 1) & 1, dz = q >> 2;
-        const int i = cl.i[0] + dx, j = cl.i[1] + dy, k = cl.i[2] + dz;
-        if ((unsigned)i >= (unsigned)g.n || (unsigned)j >= (unsigned)g.n || (unsigned)k >= (unsigned)g.n) continue;
-        const double hw = (double)(dx ? w[0] : 1.0f - w[0]) * (double)(dy ? w[1] : 1.0f - w[1]) *
-                          (double)(dz ? w[2] : 1.0f - w[2]);
-        agg_add(A, s, vidx(g, i, j, k), coef * hw, grad, g.nvox, marks, list);
-    }
-}
+using GdScatter = TileScatter<double, 1>;    // 33 KB
 
 // One frame's rows of the map-filter objective at the current means: the
 // render-through rows (same validity, gates and weights as the P1 objective)
@@ -944,17 +1131,15 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
                                                  int* __restrict__ list, double* __restrict__ partials) {
     __shared__ BlockPose sp;
     __shared__ double wsum[4];
-    __shared__ GdAgg A;
+    __shared__ GdScatter T;
     extern __shared__ __align__(16) unsigned lbits[];
-    for (int e = threadIdx.x; e < 4 * kAggSlots; e += 256) {
-        (&A.key[0][0])[e] = -1;
-        (&A.val[0][0])[e] = 0.0;
-    }
     const FreeBits fb = block_setup(g, gbits, lbits, pose, &sp);   // synchronises the workgroup
     const BlockPose& P = sp;
     int u, v, s;
-    quad_pixel(c, blockIdx.x, u, v, s);
-    double cost = 0.0;
+    scatter_pixel(c, blockIdx.x, u, v, s);
+    double cost = 0.0, k0 = 0.0, k1 = 0.0;   // k0, k1: coefficients of this lane's plane at samples k*-1, k*
+    Cell c0{}, c1{};
+    float w0[3] = {0.0f, 0.0f, 0.0f}, w1[3] = {0.0f, 0.0f, 0.0f};
     if (u < c.W && v < c.H) {
         float dir[3];
         ray_dir32(c, P.f, u, v, dir);
@@ -963,7 +1148,8 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
         const long long pix = (long long)v * c.W + u;
         const float D = obs_depth[pix];
         if (k >= 1 && depth_ok(D)) {   // the same for the four lanes of a ray
-            const Cell c0 = sample_cell(rc, k - 1), c1 = sample_cell(rc, k);
+            c0 = sample_cell(rc, k - 1);
+            c1 = sample_cell(rc, k);
             const QuadShade q = shade_quad<float, false>(g, gd, cd, P.d, u, v, map, c0, c1, k, s);
             const double r = s == 0 ? q.value - (double)D : q.value - (double)obs_rgb[3 * pix + s - 1];
             double l1 = s == 0 ? 0.0 : fabs(r);
@@ -980,7 +1166,6 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
             ga += __shfl_xor(ga, 1, 64);
             ga += __shfl_xor(ga, 2, 64);
             const double inv_den = 1.0 / (q.f1 - q.f0);
-            double k0, k1;   // coefficients of this lane's plane at the cells of samples k*-1, k*
             if (s == 0) {
                 k0 = -ga * (1.0 - q.alpha) * inv_den;
                 k1 = -ga * q.alpha * inv_den;
@@ -988,23 +1173,27 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
                 k0 = gout * (1.0 - q.alpha);
                 k1 = gout * q.alpha;
             }
-            if (k0 != 0.0) agg_cell(g, A, s, c0, q.w0, k0, grad, marks, list);
-            if (k1 != 0.0) agg_cell(g, A, s, c1, q.w1, k1, grad, marks, list);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                w0[a] = q.w0[a];
+                w1[a] = q.w1[a];
+            }
         }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) cost += __shfl_xor(cost, off, 64);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = cost;
+    // a ray contributes when one of its four lanes does
+    const int mine = k0 != 0.0 || k1 != 0.0 ? 1 : 0;
+    const bool live = quad_min(-mine) != 0;
     __syncthreads();
     if (threadIdx.x == 0) partials[blockIdx.x] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-    // one global atomic per distinct (plane, voxel) of the tile
-    for (int e = threadIdx.x; e < 4 * kAggSlots; e += 256) {
-        const int key = (&A.key[0][0])[e];
-        if (key < 0) continue;
-        const int pl = e / kAggSlots;
-        unsafeAtomicAdd(grad + (long long)pl * g.nvox + key, (&A.val[0][0])[e]);
-        mark_brick(marks, list, key >> 9);
-    }
+    Scatter<double, 1>& A = T.wave[threadIdx.x >> 6];
+    const Window w = scatter_window(g, A, live, c0, c1);
+    auto touched = [&](int b) { mark_brick(marks, list, b); };
+    scatter_cell(g, A, w, s, c0, w0, k0, live && k0 != 0.0, grad, touched);
+    scatter_cell(g, A, w, s, c1, w1, k1, live && k1 != 0.0, grad, touched);
+    scatter_flush(g, T, w, grad, touched);
 }
 
 // ---------------------------------------------------------------------------

@@ -107,23 +107,24 @@ __device__ inline void chol_inverse(const double* L, double* Ainv) {
     __syncthreads();
 }
 
-// Fixed-order block sum of partial normal equations (nblocks rows of 29
-// doubles) into lds_out[29].  The rows are read as one flat array with
-// coalesced loads: thread t < 29 G (G = row groups) reads elements t, t + 29 G,
-// ... which all belong to column t mod 29, keeping eight independent partial
+// Fixed-order block sum of partial sums (nblocks rows of NV doubles, 29 for
+// the normal equations) into lds_out[NV].  The rows are read as one flat array with
+// coalesced loads: thread t < NV G (G = row groups) reads elements t, t + NV G,
+// ... which all belong to column t mod NV, keeping eight independent partial
 // sums in flight; the G sums of each column are then added in row-group order.
 // (Each thread reading whole rows made every load instruction touch 64 cache
 // lines, which one workgroup's vector memory path takes serially.)
 // With sg given, the filter state is copied into ls on the way: its words
 // are loaded together with the first partials (not one round trip before
 // them) and stored to LDS before the sum's barrier.
+template <int NV = PRISM_NEQ>
 __device__ inline void sum_partials(const double* __restrict__ partials, int nblocks, double* lds_red,
                                     double* lds_out, const prism_filter_state* __restrict__ sg = nullptr,
                                     prism_filter_state* ls = nullptr) {
     constexpr int kStateWords = (int)(sizeof(prism_filter_state) / 8);
     static_assert(sizeof(prism_filter_state) % 8 == 0 && kStateWords <= 2 * 256, "state copied in two words per thread");
     const int bd = min((int)blockDim.x, kRedLds);
-    const int G = bd / PRISM_NEQ, span = G * PRISM_NEQ;
+    const int G = bd / NV, span = G * NV;
     const int t = threadIdx.x;
     unsigned long long sw0 = 0, sw1 = 0;
     const int t1 = t + (int)blockDim.x;
@@ -134,7 +135,7 @@ __device__ inline void sum_partials(const double* __restrict__ partials, int nbl
     }
     double acc = 0.0;
     if (t < span) {
-        const long long total = (long long)nblocks * PRISM_NEQ;
+        const long long total = (long long)nblocks * NV;
         double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         long long e = t;
         for (; e + 7LL * span < total; e += 8LL * span) {
@@ -154,9 +155,9 @@ __device__ inline void sum_partials(const double* __restrict__ partials, int nbl
         if (t1 < kStateWords) dst[t1] = sw1;
     }
     __syncthreads();
-    if (t < PRISM_NEQ) {
+    if (t < NV) {
         double sum = 0.0;
-        for (int r = 0; r < G; ++r) sum += lds_red[r * PRISM_NEQ + t];
+        for (int r = 0; r < G; ++r) sum += lds_red[r * NV + t];
         lds_out[t] = sum;
     }
     __syncthreads();
@@ -914,13 +915,13 @@ hipError_t launch_rollout(const prism_filter_state* S, const prism_filter_bias_s
     return hipSuccess;
 }
 
-// per-frame fixed-order sum of block partials; the first nvals values of
-// each frame go to out[frame * stride + q]
-__global__ __launch_bounds__(512) void k_finalize(const double* __restrict__ partials, int nblocks, int nvals,
-                                                  double* __restrict__ out, int stride) {
-    __shared__ double red[kRedLds], neq[PRISM_NEQ];
-    sum_partials(partials + (long long)blockIdx.x * nblocks * PRISM_NEQ, nblocks, red, neq);
-    if ((int)threadIdx.x < nvals) out[(long long)blockIdx.x * stride + threadIdx.x] = neq[threadIdx.x];
+// per-frame fixed-order sum of block partials (NV values each)
+template <int NV>
+__global__ __launch_bounds__(512) void k_finalize(const double* __restrict__ partials, int nblocks,
+                                                  double* __restrict__ out) {
+    __shared__ double red[kRedLds], sums[NV];
+    sum_partials<NV>(partials + (long long)blockIdx.x * nblocks * NV, nblocks, red, sums);
+    if ((int)threadIdx.x < NV) out[(long long)blockIdx.x * NV + threadIdx.x] = sums[threadIdx.x];
 }
 
 hipError_t launch_predict(prism_filter_state* S, prism_filter_bias_state* X, const double* u, const TransC& tc,
@@ -971,9 +972,13 @@ hipError_t launch_first_frame_batch(const BatchArgs& b, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, int nvals, double* out,
-                           int stride, hipStream_t st) {
-    k_finalize<<<n_frames, 512, 0, st>>>(partials, nblocks, nvals, out, stride);
+hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
+    k_finalize<PRISM_NEQ><<<n_frames, 512, 0, st>>>(partials, nblocks, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_finalize6(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
+    k_finalize<6><<<n_frames, 512, 0, st>>>(partials, nblocks, out);
     return hipGetLastError();
 }
 

@@ -408,43 +408,6 @@ __device__ inline void so3_exp_step(const double w[3], double E[9]) {
     E[7] = __builtin_fma(A, w[0], yz);
 }
 
-// x + the value of the lane a DPP control selects
-template <int Ctrl>
-__device__ __forceinline__ double add_dpp(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), Ctrl, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), Ctrl, 0xF, 0xF, false);
-    return x + __hiloint2double(hi, lo);
-}
-
-// Six sums over a wavefront without LDS: the 32-lane swap hands lanes 0-31
-// the sums of values 0-2 and lanes 32-63 those of 3-5, the row swap and four
-// DPP steps finish each half; s[0..2] are the same in every lane of a half.
-__device__ __forceinline__ void wave_sum6(const double g[6], double s[3]) {
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(g[j]),
-                                                        (unsigned)__double2loint(g[j + 3]), false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(g[j]),
-                                                        (unsigned)__double2hiint(g[j + 3]), false, false);
-        s[j] = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const unsigned lo = (unsigned)__double2loint(s[j]), hi = (unsigned)__double2hiint(s[j]);
-        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        s[j] = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-    }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x140>(s[j]);   // row mirror
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x141>(s[j]);   // half-row mirror
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x4E>(s[j]);    // lane ^ 2
-#pragma unroll
-    for (int j = 0; j < 3; ++j) s[j] = add_dpp<0xB1>(s[j]);    // lane ^ 1
-}
-
 __device__ __forceinline__ double lane_value(double x, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
                             __builtin_amdgcn_readlane(__double2loint(x), lane));

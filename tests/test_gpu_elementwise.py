@@ -319,6 +319,59 @@ def test_render_vjp_8_frames_full_size(big):
     assert em.max() <= 1e-4, em.max()
 
 
+@pytest.mark.parametrize("n,width,height,kind", [(64, 13, 9, "room"), (64, 101, 67, "room"), (64, 320, 240, "room"),
+                                                 (128, 24, 17, "room"), (16, 40, 30, "noise"), (24, 7, 5, "noise")])
+def test_scatter_boxes(n, width, height, kind):
+    """The adjoint's and the descent gradient's scatter at the sizes that
+    decide where a wavefront's sums live: pixels smaller and larger than a
+    voxel (boxes far inside and beyond a window), tiles that see surfaces far
+    apart, images that do not fill their tiles, and cells that straddle the
+    grid's boundary (noise maps).  Map gradient as in the full-size test:
+    1e-4 of the entry or of 1e-2 of the channel's largest."""
+    banner(f"scatter boxes n={n} {width}x{height} {kind}")
+    c = synth.trajectory_case(seed=3, n=n, width=width, height=height, n_samples=max(16, n // 2), n_frames=1)
+    if kind == "room":
+        mean = np.asarray(synth.gt_map(c["scene"])[0], np.float32)
+    else:
+        # a shell of solid voxels at the boundary, free inside, rough values
+        r = np.random.default_rng(9)
+        mean = r.uniform(0.2, 0.8, (4, n, n, n)).astype(np.float32)
+        mean[0] = -mean[0]
+        for a in range(3):
+            for e in (0, n - 1):
+                np.moveaxis(mean[0], a, 0)[e] = np.abs(np.moveaxis(mean[0], a, 0)[e])
+    g, cam = grid_of(c["scene"]), cam_of(c["cam"])
+    og, ocm = orc.grid_from_scene(c["scene"]), orc.cam_from(c["cam"])
+    vm = gpu_map(g, mean, np.full_like(mean, 0.5))
+    pose = synth.pose7(c["traj"].t[0], c["traj"].q[0])
+    pt = P().poses_tensor(pose)
+    fwd = P().render(g, vm, cam, pt, hit_k=True)
+    rng = np.random.default_rng(6)
+    gd = rng.normal(size=(1, height, width)).astype(np.float32)
+    gc = rng.normal(size=(1, height, width, 3)).astype(np.float32)
+    gm, gp = P().render_vjp(g, vm, cam, pt, fwd["hit_k"], t(gd), t(gc))
+    gm = P().bricks_to_dense(n, gm).cpu().numpy().astype(np.float64)
+    m64 = mean.astype(np.float64)
+    rgm, rgp = orc.render_vjp(og, m64, ocm, pose, gd[0], gc[0])
+    cmax = np.abs(rgm).reshape(4, -1).max(1)[:, None, None, None]
+    assert (cmax > 0).all()
+    em = np.abs(gm - rgm) / np.maximum(np.abs(rgm), 1e-2 * cmax)
+    print(f"[scatter] {int((rgm != 0).sum())} entries, max scaled error {em.max():.2e}", flush=True)
+    assert em.max() <= 1e-4
+    # descent through the same scatter in double precision: the order of the
+    # sums does not show, and the accumulators are left zero
+    D, C = fwd["depth"][0] + 0.02, fwd["rgb"][0] + 0.01
+    ws = P().map_gd_workspace(g, cam)
+    start, maps = vm.buf.clone(), []
+    for _ in range(2):
+        vm.buf.copy_(start)
+        P().map_gd(g, vm, cam, pt, D, C, P().Weights.make(), 3e-6, 3e-3, 2, ws)
+        assert not ws[:4 * n ** 3 * 8].view(torch.float64).any()
+        maps.append(vm.to_dense()[0])
+    assert torch.equal(maps[0], maps[1])
+    assert np.count_nonzero(maps[0].cpu().numpy() != mean) > 20
+
+
 def test_map_gd_full_size(big):
     """Descent mapping at the size of the closed-form comparison: 256^3 FP32,
     320x240, K = 128, one step from a perturbed previous belief (means of
