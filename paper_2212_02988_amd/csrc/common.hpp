@@ -93,13 +93,10 @@ constexpr int kUpdateGrid = 2048;   // workgroups of the map-update kernel
 // words of one free-space bitmap (one bit per brick)
 __host__ __device__ inline int free_words(int nb) { return (nb * nb * nb + 31) >> 5; }
 
-// LDS words a render workgroup keeps of a grid's free-space bits: both
-// bitmaps when they fit, else the plain bits (cells that span bricks are then
-// tested brick by brick), else none (no skipping)
+// LDS words a render workgroup keeps of a grid's free-space bits: the dilated
+// bitmap when it fits, else none (no skipping)
 constexpr int kMaxLdsWords = 12288;   // 48 KB
-__host__ __device__ inline int free_lds_words(int nwords) {
-    return 2 * nwords <= kMaxLdsWords ? 2 * nwords : nwords <= kMaxLdsWords ? nwords : 0;
-}
+__host__ __device__ inline int free_lds_words(int nwords) { return nwords <= kMaxLdsWords ? nwords : 0; }
 
 // ---------------------------------------------------------------------------
 // pose -> single-precision rotation/translation

@@ -68,46 +68,19 @@ __device__ __forceinline__ float occ_partial(const GridC& g, const T* occ, const
     return trilerp(v, c.w);
 }
 
-// True if the free-space bits prove that the sample's occupancy is <= 0:
-// every corner of its cell lies inside the grid and in bricks whose largest
-// occupancy mean is <= 0.  Each lerp of values <= 0 with a weight in [0, 1]
-// is <= 0 under round-to-nearest (rounding is monotonic and 0 is
-// representable), so the single-precision recipe would have produced a value
-// <= 0 as well and the sample cannot be the hit when tau == 0.
+// Free-space bits.  A sample's occupancy is proven <= 0 when every corner of
+// its cell lies inside the grid and in bricks whose largest occupancy mean is
+// <= 0: each lerp of values <= 0 with a weight in [0, 1] is <= 0 under
+// round-to-nearest (rounding is monotonic and 0 is representable), so the
+// single-precision recipe would have produced a value <= 0 as well and the
+// sample cannot be the hit when tau == 0.  Most marched samples are decided
+// by the bits alone, so that path takes only the cell's base corner and its
+// brick: every cell inside the grid reads the one dilated bit of the 2x2x2
+// bricks from its base brick, whether or not the cell spans bricks (a spanned
+// brick is in that block; a cell within one brick loses little from the
+// coarser test), so the plain bits are not needed here.  The corner addressing
+// and the weights are formed only for samples that read the map.
 __device__ __forceinline__ bool bit_of(lds_u32* bits, int b) { return (bits[b >> 5] >> (b & 31)) & 1u; }
-
-// The workgroup's LDS copy of the free-space bits: w the plain bits, then,
-// when dil > 0, the dilated bits at word offset dil (w NULL: no skipping)
-struct FreeBits {
-    lds_u32* w;
-    int dil;
-};
-
-// A cell within one brick takes the brick's bit.  A cell that spans bricks
-// lies in the 2x2x2 block of bricks of its base corner: one dilated bit
-// covers it (the same LDS read for every lane); without the dilated bits
-// each spanned brick is tested.
-__device__ __forceinline__ bool cell_free(const GridC& g, const FreeBits& fb, const CellAddr& a) {
-    if (fb.dil) return bit_of(fb.w + (a.cross ? fb.dil : 0), a.b0);
-    if (!a.cross) return bit_of(fb.w, a.b0);
-    const int sx = a.dx != 1 ? 1 : 0, sy = a.dy != 8 ? g.nb : 0, sz = a.dz != 64 ? g.nb * g.nb : 0;
-    bool all = true;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-        all &= bit_of(fb.w, a.b0 + ((q & 1) ? sx : 0) + ((q & 2) ? sy : 0) + ((q & 4) ? sz : 0));
-    return all;
-}
-
-// Occupancy of marched sample fk (an integer held in a float), or -1 when the
-// free-space bits prove it is <= 0 (fb: the workgroup's LDS copy, present
-// only when tau == 0).  Most marched samples are decided by the bits alone,
-// so that path takes only the cell's base corner and its brick: with the
-// dilated bits every cell inside the grid reads the one bit of the 2x2x2
-// bricks from its base brick, whether or not the cell spans bricks (a
-// spanned brick is in that block; a cell within one brick loses little from
-// the coarser test).  The corner addressing and the weights are formed only
-// for samples that read the map.
-enum BitsMode { kNoBits = 0, kPlainBits = 1, kDilatedBits = 2 };
 
 // grid coordinate of a marched sample and its cell's base corner
 struct SamplePos {
@@ -125,8 +98,9 @@ __device__ __forceinline__ SamplePos sample_pos(const RayCoef& rc, float fk) {
     return p;
 }
 
-template <typename T, bool Pool, int Bits, bool DilTested = false>
-__device__ __forceinline__ float march_sample(const GridC& g, const T* occ, const FreeBits& fb, const SamplePos& p) {
+// occupancy of a marched sample that the bits do not decide
+template <typename T, bool Pool>
+__device__ __forceinline__ float march_sample(const GridC& g, const T* occ, const SamplePos& p) {
     const float* gc = p.gc;
     const int* i = p.i;
     const unsigned lim = (unsigned)(g.n - 1);
@@ -134,10 +108,6 @@ __device__ __forceinline__ float march_sample(const GridC& g, const T* occ, cons
         // all 8 corners inside: indices >= 0 and < 2^10, so 24-bit products
         const unsigned bx = (unsigned)i[0] >> 3, by = (unsigned)i[1] >> 3, bz = (unsigned)i[2] >> 3;
         const int b0 = (int)(__umul24(bz, (unsigned)(g.nb * g.nb)) + __umul24(by, (unsigned)g.nb) + bx);
-        if constexpr (Bits == kDilatedBits && !DilTested) {
-            // bit b0 of the dilated bits (the bit-field extract takes the low 5 bits of b0)
-            if (__builtin_amdgcn_ubfe(fb.w[fb.dil + (b0 >> 5)], (unsigned)b0, 1u)) return -1.0f;
-        }
         const int lx = i[0] & 7, ly = i[1] & 7, lz = i[2] & 7;
         CellAddr a;
         a.b0 = b0;
@@ -146,9 +116,6 @@ __device__ __forceinline__ float march_sample(const GridC& g, const T* occ, cons
         a.dy = ly == 7 ? 512 * g.nb - 56 : 8;
         a.dz = lz == 7 ? 512 * g.nb * g.nb - 448 : 64;
         a.cross = (lx == 7) | (ly == 7) | (lz == 7);
-        // plain bits only (the dilated ones did not fit in LDS): per spanned brick
-        if constexpr (Bits == kPlainBits)
-            if (cell_free(g, fb, a)) return -1.0f;
         // inside the grid g >= 0, where g - floor(g) is exact and fract(g) equals it
         float w[3];
 #pragma unroll
@@ -207,25 +174,30 @@ struct BlockPose {
     Pose32 f;
 };
 
+// sixteen bytes of free-space bits in global memory (the dilated ones start
+// at any word)
+typedef unsigned uint4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // The prologue of a marching workgroup, one barrier: thread 0's pose loads
-// are issued first and are in flight while every thread copies the
-// free-space bits to LDS — both bitmaps when they fit, else the plain bits,
-// else none (no skipping): free_lds_words words, which the launch allocates.
-__device__ __forceinline__ FreeBits block_setup(const GridC& g, const unsigned* __restrict__ gbits, unsigned* lbits,
+// are issued first and are in flight while every thread copies the dilated
+// free-space bits to LDS (free_lds_words words, which the launch allocates;
+// none: no skipping, NULL).  gbits: the map's two bitmaps, the dilated one
+// last.  (Copying both, as the march of cells within one brick could use,
+// took a 384^3 map's workgroup 27 KB instead of 13.5, hence one workgroup
+// less per CU.)
+__device__ __forceinline__ lds_u32* block_setup(const GridC& g, const unsigned* __restrict__ gbits, unsigned* lbits,
                                                 const prism_pose* pose, BlockPose* sp) {
     prism_pose raw;
     if (threadIdx.x == 0) raw = *pose;
-    FreeBits fb{nullptr, 0};
     const int nwords = free_words(g.nb), nl = gbits ? free_lds_words(nwords) : 0;
-    if ((reinterpret_cast<uintptr_t>(gbits) & 15) == 0) {
-        // 16-byte copies (the workgroup's LDS copy is 16-byte aligned), then the tail
+    if (nl) {
+        const unsigned* src = gbits + nwords;
         const int n4 = nl >> 2;
-        const uint4* g4 = reinterpret_cast<const uint4*>(gbits);
-        uint4* l4 = reinterpret_cast<uint4*>(lbits);
-        for (int i = threadIdx.x; i < n4; i += blockDim.x) l4[i] = g4[i];
-        for (int i = (n4 << 2) + threadIdx.x; i < nl; i += blockDim.x) lbits[i] = gbits[i];
-    } else {
-        for (int i = threadIdx.x; i < nl; i += blockDim.x) lbits[i] = gbits[i];
+        for (int i = threadIdx.x; i < n4; i += blockDim.x) {
+            const uint4u v = reinterpret_cast<const uint4u*>(src)[i];
+            reinterpret_cast<uint4*>(lbits)[i] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+        for (int i = (n4 << 2) + threadIdx.x; i < nl; i += blockDim.x) lbits[i] = src[i];
     }
     if (threadIdx.x == 0) {
         quat_to_rot64(raw, sp->d.R);
@@ -233,11 +205,7 @@ __device__ __forceinline__ FreeBits block_setup(const GridC& g, const unsigned* 
         sp->f = to32(sp->d);
     }
     __syncthreads();
-    if (nl) {
-        fb.w = (lds_u32*)lbits;
-        fb.dil = nl > nwords ? nwords : 0;
-    }
-    return fb;
+    return nl ? (lds_u32*)lbits : nullptr;
 }
 
 __device__ __forceinline__ const BlockPose& block_pose(const prism_pose* pose, BlockPose* sp) {
@@ -295,9 +263,9 @@ __device__ __forceinline__ double quad_bcast0(double x) {
 
 // first sample index whose occupancy exceeds tau (strictly), or -1; every
 // lane of the quad returns the same value
-template <typename T, bool Pool, int Bits>
+template <typename T, bool Pool, bool Bits>
 __device__ __forceinline__ int march_quad_b(const GridC& g, const CamC& c, const RayCoef& rc, const T* occ,
-                                            const FreeBits& fb, int s) {
+                                            lds_u32* fb, int s) {
     constexpr int G = kLanes * kPerLane;
     // the sample index as a float, advanced exactly (K < 2^24); the last trip's
     // samples past K - 1 are evaluated like any other and ignored
@@ -317,7 +285,7 @@ __device__ __forceinline__ int march_quad_b(const GridC& g, const CamC& c, const
     for (int k0 = 0; k0 < c.K; k0 += G, fk0 += (float)G) {
         float f[kPerLane];
         bool gone = false;
-        if constexpr (Bits == kDilatedBits) {
+        if constexpr (Bits) {
             // the round's free-space tests first, as straight-line code, so its
             // LDS reads are in flight together (a sample outside the grid reads
             // word 0 and ignores it); then the samples the bits do not decide,
@@ -335,7 +303,7 @@ __device__ __forceinline__ int march_quad_b(const GridC& g, const CamC& c, const
                 const int b = (int)(__umul24((unsigned)i[2] >> 3, (unsigned)(g.nb * g.nb)) +
                                     __umul24((unsigned)i[1] >> 3, (unsigned)g.nb) + ((unsigned)i[0] >> 3));
                 b0[j] = in[j] ? b : 0;
-                word[j] = fb.w[fb.dil + (b0[j] >> 5)];
+                word[j] = fb[b0[j] >> 5];
                 if (j == kPerLane - 1) {
 #pragma unroll
                     for (int a = 0; a < 3; ++a) gone |= (i[a] < lo[a]) | (i[a] >= hi[a]);
@@ -345,13 +313,13 @@ __device__ __forceinline__ int march_quad_b(const GridC& g, const CamC& c, const
             for (int j = 0; j < kPerLane; ++j) {
                 const bool fr = in[j] && __builtin_amdgcn_ubfe(word[j], (unsigned)b0[j], 1u);
                 f[j] = fr ? -1.0f
-                          : march_sample<T, Pool, Bits, true>(g, occ, fb, sample_pos(rc, fk0 + (float)(j * kLanes)));
+                          : march_sample<T, Pool>(g, occ, sample_pos(rc, fk0 + (float)(j * kLanes)));
             }
         } else {
 #pragma unroll
             for (int j = 0; j < kPerLane; ++j) {
                 const SamplePos p = sample_pos(rc, fk0 + (float)(j * kLanes));
-                f[j] = march_sample<T, Pool, Bits>(g, occ, fb, p);
+                f[j] = march_sample<T, Pool>(g, occ, p);
                 if (j == kPerLane - 1) {
 #pragma unroll
                     for (int a = 0; a < 3; ++a) gone |= (p.i[a] < lo[a]) | (p.i[a] >= hi[a]);
@@ -372,14 +340,13 @@ __device__ __forceinline__ int march_quad_b(const GridC& g, const CamC& c, const
     return -1;
 }
 
-// the march with the workgroup's free-space bits mode fixed (one uniform
+// the march with or without the workgroup's free-space bits (one uniform
 // branch per ray instead of one per sample)
 template <typename T, bool Pool>
-__device__ __forceinline__ int march_quad(const GridC& g, const CamC& c, const RayCoef& rc, const T* occ,
-                                          const FreeBits& fb, int s) {
-    if (fb.w && fb.dil) return march_quad_b<T, Pool, kDilatedBits>(g, c, rc, occ, fb, s);
-    if (fb.w) return march_quad_b<T, Pool, kPlainBits>(g, c, rc, occ, fb, s);
-    return march_quad_b<T, Pool, kNoBits>(g, c, rc, occ, fb, s);
+__device__ __forceinline__ int march_quad(const GridC& g, const CamC& c, const RayCoef& rc, const T* occ, lds_u32* fb,
+                                          int s) {
+    if (fb) return march_quad_b<T, Pool, true>(g, c, rc, occ, fb, s);
+    return march_quad_b<T, Pool, false>(g, c, rc, occ, fb, s);
 }
 
 // This lane's share of the shading at a valid hit: plane s (0 occupancy,
@@ -521,7 +488,7 @@ __device__ __forceinline__ void render_block(int blk, int frame, const GridC& g,
                                              uint8_t* __restrict__ mask, int32_t* __restrict__ hit_k) {
     __shared__ BlockPose sp;
     extern __shared__ __align__(16) unsigned lbits[];
-    const FreeBits fb = block_setup(g, gbits, lbits, pose, &sp);
+    lds_u32* const fb = block_setup(g, gbits, lbits, pose, &sp);
     const BlockPose& P = sp;
     int u, v, s;
     quad_pixel(c, blk, u, v, s);
@@ -664,7 +631,7 @@ __device__ __forceinline__ void render_jac_block(int blk, int frame, const GridC
     __shared__ BlockPose sp;
     __shared__ double lds[kRedLds];
     extern __shared__ __align__(16) unsigned lbits[];
-    const FreeBits fb = block_setup(g, gbits, lbits, pose, &sp);
+    lds_u32* const fb = block_setup(g, gbits, lbits, pose, &sp);
     const BlockPose& P = sp;
     int u, v, s;
     quad_pixel(c, blk, u, v, s);
@@ -1133,7 +1100,7 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
     __shared__ double wsum[4];
     __shared__ GdScatter T;
     extern __shared__ __align__(16) unsigned lbits[];
-    const FreeBits fb = block_setup(g, gbits, lbits, pose, &sp);   // synchronises the workgroup
+    lds_u32* const fb = block_setup(g, gbits, lbits, pose, &sp);   // synchronises the workgroup
     const BlockPose& P = sp;
     int u, v, s;
     scatter_pixel(c, blockIdx.x, u, v, s);
@@ -1226,7 +1193,7 @@ hipError_t launch_render(const GridC& g, const CamC& c, const GridD& gd, const C
 }
 
 hipError_t launch_render_batch(const BatchArgs& b, int dtype, bool pool, int max_lds_words, hipStream_t st) {
-    // every filter copies free_lds_words of its bits to LDS (block_setup):
+    // every filter copies free_lds_words of its dilated bits to LDS (block_setup):
     // the allocation is the largest of these over the batch
     size_t lds = (size_t)max_lds_words * 4;
     if (dtype == PRISM_BF16 && pool)
