@@ -136,6 +136,8 @@ CamC cam_c(const prism_camera* c) {
     o.W = c->width;
     o.H = c->height;
     o.K = c->n_samples;
+    const unsigned tiles = (unsigned)(c->width + 7) / 8;
+    o.tiles_inv = tiles > 1 ? (unsigned)((1ull << 32) / tiles) + 1 : 0;
     return o;
 }
 

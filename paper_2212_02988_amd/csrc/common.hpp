@@ -51,6 +51,7 @@ struct CamC {
     float ifx, ify, fx, fy, cx, cy;
     float dn, dstep, tau;
     int W, H, K;
+    unsigned tiles_inv;   // floor(2^32 / ceil(W / 8)) + 1, or 0 for one 8x8 tile per row
 };
 
 // Double-precision copies of the parameters for the value path: once the
