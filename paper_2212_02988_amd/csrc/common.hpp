@@ -325,6 +325,42 @@ __device__ __forceinline__ void corners_in_g(gptr<T> plane, const CellAddr& a, f
     v[7] = ldg(plane, o + dz + dy + dx);
 }
 
+// Corners of a cell inside the grid in a brick-pool map, through the slots of
+// the bricks it spans (a third of all cells span more than one).  A lane whose
+// cell lies in one brick reads one table entry; one that spans bricks reads
+// the other corners' as well, all of them in flight together.  Corner offsets
+// within a brick are formed per axis and the loads are unconditional (a brick
+// without a slot reads slot 0 and is replaced by the prior value): about 60
+// instructions, where testing and indexing each corner on its own took 200.
+template <typename T>
+__device__ __forceinline__ void corners_pool(const GridC& g, gptr<T> plane, const CellAddr& a, float priorv,
+                                             float v[8]) {
+    const int b0 = a.b0;
+    const gptr<int> table = as_global(g.table);
+    auto slot_of = [&](int b) { return *(gptr<int>)((gptr<char>)table + (unsigned)b * 4u); };
+    int slot[8];
+    slot[0] = slot_of(b0);
+    if (a.cross) {
+        // +x, +y, +z neighbours of a corner on a brick's last voxel
+        const int sx = a.dx != 1 ? 1 : 0, sy = a.dy != 8 ? g.nb : 0, sz = a.dz != 64 ? g.nb * g.nb : 0;
+#pragma unroll
+        for (int q = 1; q < 8; ++q)
+            slot[q] = slot_of(b0 + ((q & 1) ? sx : 0) + ((q & 2) ? sy : 0) + ((q & 4) ? sz : 0));
+    } else {
+#pragma unroll
+        for (int q = 1; q < 8; ++q) slot[q] = slot[0];
+    }
+    const unsigned l = (unsigned)a.base & 511u;
+    const unsigned x1 = (l + 1) & 7u, y1 = (l + 8) & 56u, z1 = (l + 64) & 448u;
+    const unsigned xs[2] = {l & 7u, x1}, ys[2] = {l & 56u, y1}, zs[2] = {l & 448u, z1};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const unsigned at = ((unsigned)max(slot[q], 0) << 9) | xs[q & 1] | ys[(q >> 1) & 1] | zs[q >> 2];
+        const float x = ldg(plane, at * (unsigned)sizeof(T));
+        v[q] = slot[q] < 0 ? priorv : x;
+    }
+}
+
 // 8 corner values of one plane: out-of-grid corners take `outv`, corners in
 // bricks without a slot (brick-pool maps) `priorv`
 template <typename T, bool Pool>
@@ -336,17 +372,8 @@ __device__ __forceinline__ void corners(const GridC& g, const T* plane, const Ce
             corners_in_g(as_global(plane), a, v);
             return;
         }
-        if (!a.cross) {
-            // one brick: its slot, then the dense steps inside it
-            const int slot = g.table[a.b0];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = priorv;
-            if (slot >= 0) {
-                a.base = (slot << 9) | (a.base & 511);
-                corners_in_g(as_global(plane), a, v);
-            }
-            return;
-        }
+        corners_pool(g, as_global(plane), a, priorv, v);
+        return;
     }
     bool okx0 = (unsigned)c.i[0] < (unsigned)g.n, okx1 = (unsigned)(c.i[0] + 1) < (unsigned)g.n;
     bool oky0 = (unsigned)c.i[1] < (unsigned)g.n, oky1 = (unsigned)(c.i[1] + 1) < (unsigned)g.n;

@@ -124,23 +124,11 @@ __device__ __forceinline__ float march_sample(const GridC& g, const T* occ, cons
         float w[3];
 #pragma unroll
         for (int q = 0; q < 3; ++q) w[q] = __builtin_amdgcn_fractf(gc[q]);
-        if constexpr (Pool) {
-            // brick-pool map: a single-brick cell through its slot (a brick
-            // without one reads as the prior everywhere, and the trilinear
-            // blend of equal values is that value); others corner by corner
-            if (!a.cross) {
-                const int slot = g.table[b0];
-                if (slot < 0) return g.pocc;
-                a.base = (slot << 9) | (a.base & 511);
-            } else {
-                Cell cl;
-#pragma unroll
-                for (int q = 0; q < 3; ++q) { cl.i[q] = i[q]; cl.w[q] = w[q]; }
-                return occ_at<T, Pool>(g, occ, cl);
-            }
-        }
         float v[8];
-        corners_in_g(as_global(occ), a, v);
+        if constexpr (Pool)
+            corners_pool(g, as_global(occ), a, g.pocc, v);
+        else
+            corners_in_g(as_global(occ), a, v);
         return trilerp(v, w);
     }
     // Every corner outside the grid (on some axis both i and i + 1 are): the
