@@ -144,8 +144,7 @@ struct Rel32 {
     Pose64 cur, prev;      // both poses in double precision (values)
 };
 
-__device__ __forceinline__ void rel_of(const prism_pose* pose, const prism_pose* pose_prev, Rel32& rel) {
-    Pose64 P = load_pose64(pose), Q = load_pose64(pose_prev);
+__device__ __forceinline__ void rel_of(const Pose64& P, const Pose64& Q, Rel32& rel) {
     double d[3] = {P.t[0] - Q.t[0], P.t[1] - Q.t[1], P.t[2] - Q.t[2]};
     for (int a = 0; a < 3; ++a) {
         for (int b = 0; b < 3; ++b)
@@ -154,6 +153,10 @@ __device__ __forceinline__ void rel_of(const prism_pose* pose, const prism_pose*
     }
     rel.cur = P;
     rel.prev = Q;
+}
+
+__device__ __forceinline__ void rel_of(const prism_pose* pose, const prism_pose* pose_prev, Rel32& rel) {
+    rel_of(load_pose64(pose), load_pose64(pose_prev), rel);
 }
 
 __device__ __forceinline__ void pixel_dir64(const CamD& c, int u, int v, double r[3]) {
@@ -453,6 +456,13 @@ __device__ __forceinline__ void wave_sum6(const double g[6], double s[3]) {
     for (int j = 0; j < 3; ++j) s[j] = add_dpp<0x4E>(s[j]);    // lane ^ 2
 #pragma unroll
     for (int j = 0; j < 3; ++j) s[j] = add_dpp<0xB1>(s[j]);    // lane ^ 1
+}
+
+// LDS operations of a wavefront take effect in program order; this keeps the
+// compiler from moving them across each other (no instruction)
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 constexpr int kRedLds = 32 * 16;   // doubles of LDS scratch for block_reduce29

@@ -831,13 +831,6 @@ struct TileScatter {
     int mark[256];   // bricks of a box that goes out (of each window's 64, when they go out one by one)
 };
 
-// LDS operations of a wavefront take effect in program order; this keeps the
-// compiler from moving them across each other (no instruction)
-__device__ __forceinline__ void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // pixels of a scattering wavefront: 4x4, four wavefronts per 8x8 tile
 __device__ __forceinline__ void scatter_pixel(const Tile& tl, int& u, int& v, int& s) {
     const int t = threadIdx.x, r = (t >> 2) & 15, wv = t >> 6;

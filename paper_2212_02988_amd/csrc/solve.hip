@@ -5,12 +5,15 @@
 // and the product with the velocity conditional; the same over the 15-D
 // state with an accelerometer bias; predictive rollouts.
 //
-// Each kernel is one workgroup per filter (256 threads for the prediction,
-// 512 for the Gauss-Newton and Laplace kernels, which first reduce the block
-// partial sums of the normal equations in a fixed order): matrix products
-// are spread over the threads, and the small Cholesky factorisations run on
-// one thread.  Everything stays on the device so a filter step can be
-// captured in a HIP graph.
+// Each kernel is one workgroup per filter (256 threads for the prediction;
+// the Gauss-Newton and Laplace kernels reduce the block partial sums of the
+// normal equations in a fixed order with 512, while a ninth wavefront forms
+// what does not depend on them).  What remains is a chain of dependent double-
+// precision operations, so it is kept short: small factorisations run in the
+// registers of one wavefront with reciprocal roots, matrix products are
+// spread over the threads with only their non-zero terms, and independent
+// chains run in different wavefronts.  Everything stays on the device so a
+// filter step can be captured in a HIP graph.
 #include "common.hpp"
 #include "launch.hpp"
 #include "se3.hpp"
@@ -55,8 +58,8 @@ __device__ inline bool chol(double* A) {
 #pragma unroll
         for (int k = 0; k < j; ++k) s -= A[j * N + k] * A[j * N + k];
         ok = ok && (s > 0.0);
-        double d = sqrt(fmax(s, 1e-300));
-        double id = 1.0 / d;
+        double d;
+        const double id = rsqrt64(fmax(s, 1e-300), &d);
         A[j * N + j] = d;
 #pragma unroll
         for (int i = j + 1; i < N; ++i) {
@@ -71,107 +74,146 @@ __device__ inline bool chol(double* A) {
     return ok;
 }
 
-// solve L L^T x = b in place (single thread)
+// Lower Cholesky factor of an N x N matrix in the registers of every lane of a
+// wavefront (A: LDS or registers, row-major), with the reciprocals of its
+// diagonal: a reciprocal root serves the diagonal and its inverse.  False if
+// not positive definite (the same for all lanes).
 template <int N>
-__device__ inline void chol_solve(const double* L, double* b) {
-    double id[N];
+struct Chol {
+    double L[N][N], id[N];
+};
+template <int N>
+__device__ __forceinline__ bool chol_regs(const double* A, Chol<N>& c) {
+    bool ok = true;
 #pragma unroll
-    for (int i = 0; i < N; ++i) id[i] = 1.0 / L[i * N + i];
+    for (int j = 0; j < N; ++j) {
+        double s = A[j * N + j];
+#pragma unroll
+        for (int k = 0; k < j; ++k) s -= c.L[j][k] * c.L[j][k];
+        ok = ok && (s > 0.0);
+        double d;
+        const double r = rsqrt64(fmax(s, 1e-300), &d);
+        c.L[j][j] = d;
+        c.id[j] = r;
+#pragma unroll
+        for (int i = j + 1; i < N; ++i) {
+            double t = A[i * N + j];
+#pragma unroll
+            for (int k = 0; k < j; ++k) t -= c.L[i][k] * c.L[j][k];
+            c.L[i][j] = t * r;
+        }
+    }
+    return ok;
+}
+
+// solve L L^T x = b in place
+template <int N>
+__device__ __forceinline__ void chol_solve(const Chol<N>& c, double b[N]) {
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         double s = b[i];
 #pragma unroll
-        for (int k = 0; k < i; ++k) s -= L[i * N + k] * b[k];
-        b[i] = s * id[i];
+        for (int k = 0; k < i; ++k) s -= c.L[i][k] * b[k];
+        b[i] = s * c.id[i];
     }
 #pragma unroll
     for (int i = N - 1; i >= 0; --i) {
         double s = b[i];
 #pragma unroll
-        for (int k = i + 1; k < N; ++k) s -= L[k * N + i] * b[k];
-        b[i] = s * id[i];
+        for (int k = i + 1; k < N; ++k) s -= c.L[k][i] * b[k];
+        b[i] = s * c.id[i];
     }
 }
 
-// inverse from the Cholesky factor (in LDS), one column per thread (< N)
+// inverse of a symmetric positive definite matrix, symmetrised: A -> Ainv (both
+// LDS, row-major), by one wavefront, a column per lane (N * N <= 64); false if
+// not positive definite
 template <int N>
-__device__ inline void chol_inverse(const double* L, double* Ainv) {
-    if ((int)threadIdx.x < N) {
-        double x[N];
+__device__ __forceinline__ bool spd_inverse_wave(const double* A, double* Ainv) {
+    const int lane = threadIdx.x & 63;
+    Chol<N> c;
+    const bool ok = chol_regs<N>(A, c);
+    double x[N];
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[i] = (i == (int)threadIdx.x) ? 1.0 : 0.0;
-        chol_solve<N>(L, x);
+    for (int i = 0; i < N; ++i) x[i] = i == lane ? 1.0 : 0.0;
+    chol_solve<N>(c, x);
+    wave_lds_order();   // (Ainv may be A)
+    if (lane < N)
 #pragma unroll
-        for (int i = 0; i < N; ++i) Ainv[i * N + threadIdx.x] = x[i];
-    }
-    __syncthreads();
+        for (int i = 0; i < N; ++i) Ainv[i * N + lane] = x[i];
+    wave_lds_order();
+    double s = 0.0;
+    if (lane < N * N) s = 0.5 * (Ainv[lane] + Ainv[(lane % N) * N + lane / N]);
+    wave_lds_order();
+    if (lane < N * N) Ainv[lane] = s;
+    return ok;
+}
+
+// entry (i, j) of the symmetric 6x6 matrix packed by rows of its upper triangle
+__device__ __forceinline__ int sym6(int i, int j) {
+    const int a = i < j ? i : j, b = i < j ? j : i;
+    return a * 6 - a * (a - 1) / 2 + b - a;
 }
 
 // Fixed-order block sum of partial sums (nblocks rows of NV doubles, 29 for
-// the normal equations) into lds_out[NV].  The rows are read as one flat array with
-// coalesced loads: thread t < NV G (G = row groups) reads elements t, t + NV G,
-// ... which all belong to column t mod NV, keeping eight independent partial
-// sums in flight; the G sums of each column are then added in row-group order.
-// (Each thread reading whole rows made every load instruction touch 64 cache
-// lines, which one workgroup's vector memory path takes serially.)
+// the normal equations) into lds_out[NV], by the first kSumThreads threads of
+// the workgroup (the others only meet the barriers).  The rows are read as one
+// flat array with coalesced loads: thread t < NV G (G = row groups) reads
+// elements t, t + NV G, ... which all belong to column t mod NV; the G sums of
+// each column are then added in row-group order.  (Each thread reading whole
+// rows made every load instruction touch 64 cache lines, which one workgroup's
+// vector memory path takes serially.)  One workgroup reads at the latency of
+// its rounds, so a round is 20 loads per thread, which covers a 320x240 frame's
+// 300 rows, and the next round is requested before this one is added.
+// lds_red: kSumThreads doubles.
 // With sg given, the filter state is copied into ls on the way: its words
 // are loaded together with the first partials (not one round trip before
 // them) and stored to LDS before the sum's barrier.
+constexpr int kSumThreads = 512;
+
 template <int NV = PRISM_NEQ>
 __device__ inline void sum_partials(const double* __restrict__ partials, int nblocks, double* lds_red,
                                     double* lds_out, const prism_filter_state* __restrict__ sg = nullptr,
                                     prism_filter_state* ls = nullptr) {
     constexpr int kStateWords = (int)(sizeof(prism_filter_state) / 8);
-    static_assert(sizeof(prism_filter_state) % 8 == 0 && kStateWords <= 2 * 256, "state copied in two words per thread");
-    const int bd = min((int)blockDim.x, kRedLds);
-    const int G = bd / NV, span = G * NV;
+    static_assert(sizeof(prism_filter_state) % 8 == 0 && kStateWords <= kSumThreads, "a state word per thread");
+    constexpr int G = kSumThreads / NV, span = G * NV, kRound = 20;
     const int t = threadIdx.x;
-    unsigned long long sw0 = 0, sw1 = 0;
-    const int t1 = t + (int)blockDim.x;
-    if (sg) {
-        const unsigned long long* src = reinterpret_cast<const unsigned long long*>(sg);
-        if (t < kStateWords) sw0 = src[t];
-        if (t1 < kStateWords) sw1 = src[t1];
-    }
-    double acc = 0.0;
+    unsigned long long sw = 0;
+    if (sg && t < kStateWords) sw = reinterpret_cast<const unsigned long long*>(sg)[t];
     if (t < span) {
-        const long long total = (long long)nblocks * NV;
-        double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        long long e = t;
-        for (; e + 7LL * span < total; e += 8LL * span) {
-            double x[8];
+        const int total = nblocks * NV;   // at most 2^20 rows of 29
+        double x[kRound], a[4] = {0.0, 0.0, 0.0, 0.0};
+        auto load = [&](int e0) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = partials[e + u * (long long)span];
+            for (int u = 0; u < kRound; ++u) {
+                const int e = e0 + u * span;
+                x[u] = e < total ? partials[e] : 0.0;
+            }
+        };
+        load(t);
+        for (int e0 = t; e0 < total; e0 += kRound * span) {
+            double y[kRound];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] += x[u];
+            for (int u = 0; u < kRound; ++u) y[u] = x[u];
+            if (e0 + kRound * span < total) load(e0 + kRound * span);
+#pragma unroll
+            for (int u = 0; u < kRound; ++u) a[u & 3] += y[u];
         }
-        for (; e < total; e += span) a[0] += partials[e];
-        acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-        lds_red[t] = acc;
+        lds_red[t] = (a[0] + a[1]) + (a[2] + a[3]);
     }
-    if (ls) {
-        unsigned long long* dst = reinterpret_cast<unsigned long long*>(ls);
-        if (t < kStateWords) dst[t] = sw0;
-        if (t1 < kStateWords) dst[t1] = sw1;
-    }
+    if (ls && t < kStateWords) reinterpret_cast<unsigned long long*>(ls)[t] = sw;
     __syncthreads();
     if (t < NV) {
+        double r[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) r[k] = lds_red[k * NV + t];
         double sum = 0.0;
-        for (int r = 0; r < G; ++r) sum += lds_red[r * NV + t];
+#pragma unroll
+        for (int k = 0; k < G; ++k) sum += r[k];
         lds_out[t] = sum;
     }
     __syncthreads();
-}
-
-__device__ inline void unpack_H(const double* neq, double* H, double* g) {
-    int q = 0;
-    for (int a = 0; a < 6; ++a)
-        for (int b = a; b < 6; ++b) {
-            H[a * 6 + b] = neq[q];
-            H[b * 6 + a] = neq[q];
-            ++q;
-        }
-    for (int a = 0; a < 6; ++a) g[a] = neq[21 + a];
 }
 
 // The state lives in global memory; each kernel copies it into LDS once
@@ -220,75 +262,138 @@ __device__ inline void transition_mean_t0(const prism_pose& pose, const double* 
 
 // Covariance of the linearised transition (App. E.2), whole workgroup:
 // T2 = M P M^T + G Q G^T (symmetrised) in the error state (dt, dtheta, dv,
-// dw), with E, Jl from transition_mean_t0; P, M, G, T1, T2: LDS [144].
+// dw), with E, Jl from transition_mean_t0; P, T1, T2: LDS [144].  M and G are
+// mostly zeros and ones:
+//   M = [I 0 dt I 0; 0 E 0 dt Jl; 0 0 I 0; 0 0 0 I],  G = M with E = I,
+// so only their non-zero terms are summed, in the order of the full product.
+__device__ __forceinline__ double cov_row(const double* E, const double* Jl, double dt, int i, const double* col,
+                                          int step) {
+    if (i < 3) return col[i * step] + dt * col[(6 + i) * step];
+    if (i >= 6) return col[i * step];
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s += E[(i - 3) * 3 + q] * col[(3 + q) * step];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s += dt * Jl[(i - 3) * 3 + q] * col[(9 + q) * step];
+    return s;
+}
+__device__ __forceinline__ double cov_noise(const double* Jl, const TransC& tc, int i, int j) {
+    if (i > j) {
+        const int k = i;
+        i = j;
+        j = k;
+    }
+    if (i < 3) return j == i ? tc.q[i] + tc.dt * tc.q[6 + i] * tc.dt : j == 6 + i ? tc.dt * tc.q[6 + i] : 0.0;
+    if (i >= 6) return i == j ? tc.q[i] : 0.0;
+    if (j >= 9) return tc.dt * Jl[(i - 3) * 3 + j - 9] * tc.q[j];
+    if (j >= 6) return 0.0;
+    double s = i == j ? tc.q[i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s += tc.dt * Jl[(i - 3) * 3 + q] * tc.q[9 + q] * (tc.dt * Jl[(j - 3) * 3 + q]);
+    return s;
+}
 __device__ inline void transition_cov(const double* E, const double* Jl, const TransC& tc, const double* P,
-                                      double* M, double* G, double* T1, double* T2) {
+                                      double* T1, double* T2) {
+    for (int e = threadIdx.x; e < 144; e += blockDim.x) T1[e] = cov_row(E, Jl, tc.dt, e / 12, P + e % 12, 12);   // M P
+    __syncthreads();
     for (int e = threadIdx.x; e < 144; e += blockDim.x) {
-        M[e] = 0.0;
-        G[e] = 0.0;
+        const int i = e / 12, j = e % 12;
+        if (i > j) continue;
+        const double q = cov_noise(Jl, tc, i, j);
+        const double a = cov_row(E, Jl, tc.dt, j, T1 + i * 12, 1) + q;
+        const double b = cov_row(E, Jl, tc.dt, i, T1 + j * 12, 1) + q;
+        const double s = i == j ? a : 0.5 * (a + b);
+        T2[i * 12 + j] = s;
+        T2[j * 12 + i] = s;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 0; i < 3; ++i) {
-            M[i * 12 + i] = 1.0;
-            M[i * 12 + 6 + i] = tc.dt;
-            M[(6 + i) * 12 + 6 + i] = 1.0;
-            M[(9 + i) * 12 + 9 + i] = 1.0;
-            G[i * 12 + i] = 1.0;
-            G[i * 12 + 6 + i] = tc.dt;
-            G[(3 + i) * 12 + 3 + i] = 1.0;
-            G[(6 + i) * 12 + 6 + i] = 1.0;
-            G[(9 + i) * 12 + 9 + i] = 1.0;
-            for (int j = 0; j < 3; ++j) {
-                M[(3 + i) * 12 + 3 + j] = E[i * 3 + j];
-                M[(3 + i) * 12 + 9 + j] = tc.dt * Jl[i * 3 + j];
-                G[(3 + i) * 12 + 9 + j] = tc.dt * Jl[i * 3 + j];
-            }
-        }
-    }
-    __syncthreads();
-    mm(M, P, T1, 12, 12, 12, false);       // M P
-    mm(T1, M, T2, 12, 12, 12, true);       // M P M^T
-    // G Q G^T with Q diagonal
-    for (int e = threadIdx.x; e < 144; e += blockDim.x) {
-        int i = e / 12, j = e % 12;
-        double s = 0.0;
-        for (int q = 0; q < 12; ++q) s += G[i * 12 + q] * tc.q[q] * G[j * 12 + q];
-        T2[e] += s;
-    }
-    __syncthreads();
-    symmetrize(T2, 12);
 }
 
+// put(i, j) = D + sign X W^T, symmetrised, its pairs spread over the threads
+// (X [n x 6]; W(j, q) and D(i, j) read an entry)
+template <typename GetW, typename GetD, typename Put>
+__device__ __forceinline__ void sym_plus_outer(int n, double sign, const double* X, const GetW& W, const GetD& D,
+                                               const Put& put) {
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
+        const int i = e / n, j = e % n;
+        if (i > j) continue;
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            a += X[i * 6 + q] * W(j, q);
+            b += X[j * 6 + q] * W(i, q);
+        }
+        a = D(i, j) + sign * a;
+        b = D(j, i) + sign * b;
+        const double s = i == j ? a : 0.5 * (a + b);
+        put(i, j, s);
+        put(j, i, s);
+    }
+}
+
+// 22 000 -> 9 000 clocks: the rotation's exponential comes first, and the new
+// pose (its quaternion and its relation to the anchor) is formed in the second
+// wavefront while the first inverts the pose block.
 __device__ __forceinline__ void predict_block(prism_filter_state* __restrict__ Sg, const double* __restrict__ u,
                                               const TransC& tc, Rel32* __restrict__ rel) {
-    __shared__ double M[144], G[144], T1[144], T2[144], P[144], Spp[36], L[36], Sinv[36];
+    __shared__ double T1[144], T2[144], Spp[36], Sinv[36], D[36];
     __shared__ double vnew[6], E[9], Jl[9];
     __shared__ int ok;
     __shared__ prism_filter_state Ls;
     state_in(Sg, &Ls);
     prism_filter_state* S = &Ls;
-    if (threadIdx.x == 0) {
-        S->flags = 0;
-        for (int i = 0; i < 6; ++i) S->u[i] = u[i];
-        prism_pose pr;
-        transition_mean_t0(S->pose, S->v, S->w, u, tc, vnew, E, Jl, pr);
-        S->prior = pr;
-        S->iter = pr;
-        if (rel) rel_of(&S->iter, &S->anchor, *rel);
-        for (int i = 0; i < 6; ++i) S->vel_prior[i] = vnew[i];
+    const int wv = threadIdx.x >> 6;
+    if (wv == 0) {
+        double vn[6], Ex[9], Jx[9];
+        for (int i = 0; i < 3; ++i) {
+            vn[i] = S->v[i] + u[i] * tc.du;
+            vn[3 + i] = S->w[i] + u[3 + i] * tc.du;
+        }
+        const double phi[3] = {vn[3] * tc.dt, vn[4] * tc.dt, vn[5] * tc.dt};
+        so3_exp(phi, Ex, Jx);
+        if (threadIdx.x == 0) {
+            for (int i = 0; i < 6; ++i) vnew[i] = vn[i];
+            for (int e = 0; e < 9; ++e) {
+                E[e] = Ex[e];
+                Jl[e] = Jx[e];
+            }
+        }
     }
-    for (int e = threadIdx.x; e < 144; e += blockDim.x) P[e] = S->P[e];
     __syncthreads();
-    transition_cov(E, Jl, tc, P, M, G, T1, T2);
+    transition_cov(E, Jl, tc, S->P, T1, T2);
     // split: Spp, D = Svp Spp^-1, Sv = Svv - D Svp^T
-    for (int e = threadIdx.x; e < 36; e += blockDim.x) {
-        int i = e / 6, j = e % 6;
-        Spp[e] = T2[i * 12 + j];
-        L[e] = T2[i * 12 + j];
+    if (wv == 0) {
+        const int l = threadIdx.x;
+        if (l < 36) Spp[l] = T2[(l / 6) * 12 + l % 6];
+        wave_lds_order();
+        const bool pd = spd_inverse_wave<6>(Spp, Sinv);
+        if (l == 0) ok = pd;
+    } else if (wv == 1) {
+        double R[9], R2[9];
+        prism_pose pr;
+        quat_to_R9(S->pose.q, R);
+        mat3mul(E, R, R2);
+        Pose64 cur;
+        for (int i = 0; i < 3; ++i) {
+            pr.t[i] = S->pose.t[i] + vnew[i] * tc.dt;
+            cur.t[i] = pr.t[i];
+            for (int k = 0; k < 3; ++k) cur.R[i][k] = R2[i * 3 + k];
+        }
+        const Pose64 anchor = load_pose64(&S->anchor);
+        R9_to_quat(R2, pr.q);
+        if (threadIdx.x == 64) {
+            if (rel) rel_of(cur, anchor, *rel);
+            S->prior = pr;
+            S->iter = pr;
+            S->flags = 0;
+        }
+    } else if (wv == 2) {
+        const int l = threadIdx.x & 63;
+        if (l < 6) {
+            S->u[l] = u[l];
+            S->vel_prior[l] = vnew[l];
+        }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) ok = chol<6>(L);
     __syncthreads();
     if (!ok) {
         // the predicted pose block is not positive definite: the step keeps
@@ -299,29 +404,19 @@ __device__ __forceinline__ void predict_block(prism_filter_state* __restrict__ S
         state_out(S, Sg);
         return;
     }
-    chol_inverse<6>(L, Sinv);
-    symmetrize(Sinv, 6);
-    // D = Svp Sinv
-    for (int e = threadIdx.x; e < 36; e += blockDim.x) {
-        int i = e / 6, j = e % 6;
+    if (threadIdx.x < 36) {
+        const int i = threadIdx.x / 6, j = threadIdx.x % 6;
         double s = 0.0;
+#pragma unroll
         for (int q = 0; q < 6; ++q) s += T2[(6 + i) * 12 + q] * Sinv[q * 6 + j];
-        T1[e] = s;   // D
+        D[threadIdx.x] = s;
+        S->D[threadIdx.x] = s;
+        S->Lp[threadIdx.x] = Sinv[threadIdx.x];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 36; e += blockDim.x) {
-        int i = e / 6, j = e % 6;
-        double s = 0.0;
-        for (int q = 0; q < 6; ++q) s += T1[i * 6 + q] * T2[(6 + j) * 12 + q];
-        P[e] = T2[(6 + i) * 12 + 6 + j] - s;   // Sv (reuse P)
-    }
-    __syncthreads();
-    symmetrize(P, 6);
-    for (int e = threadIdx.x; e < 36; e += blockDim.x) {
-        S->Lp[e] = Sinv[e];
-        S->D[e] = T1[e];
-        S->Sv[e] = P[e];
-    }
+    sym_plus_outer(6, -1.0, D, [&](int j, int q) { return T2[(6 + j) * 12 + q]; },
+                   [&](int i, int j) { return T2[(6 + i) * 12 + 6 + j]; },
+                   [&](int i, int j, double s) { S->Sv[i * 6 + j] = s; });
     state_out(S, Sg);
 }
 
@@ -433,7 +528,10 @@ __device__ __forceinline__ void predict_block_bias(prism_filter_state* __restric
     if (threadIdx.x < 6) X->rest_prior[threadIdx.x] = vnew[threadIdx.x];
     else if (threadIdx.x < NR) X->rest_prior[threadIdx.x] = b[threadIdx.x - 6];
     __syncthreads();
-    if (threadIdx.x == 0) ok = chol<6>(L);
+    if (threadIdx.x < 64) {
+        const bool pd = spd_inverse_wave<6>(L, Sinv);
+        if (threadIdx.x == 0) ok = pd;
+    }
     __syncthreads();
     if (!ok) {
         // no MAP problem: the step keeps the predicted mean and covariance
@@ -441,8 +539,6 @@ __device__ __forceinline__ void predict_block_bias(prism_filter_state* __restric
         state_out(S, Sg);
         return;
     }
-    chol_inverse<6>(L, Sinv);
-    symmetrize(Sinv, 6);
     // D = P_rp Sinv [9 x 6], Sv = P_rr - D P_rp^T [9 x 9]
     for (int e = threadIdx.x; e < NR * 6; e += blockDim.x) {
         int i = e / 6, j = e % 6;
@@ -477,50 +573,91 @@ __global__ __launch_bounds__(256) void k_predict(prism_filter_state* __restrict_
 // ---------------------------------------------------------------------------
 // one Gauss-Newton step of the MAP pose objective
 // ---------------------------------------------------------------------------
-// thread 0: one Gauss-Newton step on the state copy
-__device__ inline void gn_step_body(prism_filter_state* S, const double* neq) {
-    if (S->flags & PRISM_FLAG_CHOL_FALLBACK) return;
-    if (!(neq[28] > 0.0)) S->flags |= PRISM_FLAG_NO_VALID_PIXELS;
-    double H[36], g[6], A[36], b[6], e[6];
-    unpack_H(neq, H, g);
-    prism_pose it = S->iter, pr = S->prior;
-    pose_err(it, pr, e);
-    for (int i = 0; i < 6; ++i) {
-        double le = 0.0;
-        for (int j = 0; j < 6; ++j) {
-            A[i * 6 + j] = 2.0 * H[i * 6 + j] + S->Lp[i * 6 + j];
-            le += S->Lp[i * 6 + j] * e[j];
-        }
-        b[i] = -(2.0 * g[i] + le);
-    }
-    if (!chol<6>(A)) {
-        S->flags |= PRISM_FLAG_CHOL_FALLBACK;
-        S->iter = pr;
-        return;
-    }
-    chol_solve<6>(A, b);
-    retract(it, b);
-    S->iter = it;
-}
+// What does not depend on the normal equations (the error of the iterate to the
+// prior, its rotation, the anchor's) is formed by the ninth wavefront while the
+// others sum them; the first then solves in registers.  16 000 -> 7 000 clocks
+// at 300 partial rows, 26 000 -> 11 000 at 1200.
+constexpr int kSolveThreads = kSumThreads + 64;
+
+struct GnPrep {
+    double le[6], Lp[36], R[9], t[3];   // Lp e; prior precision; the iterate
+    Pose64 anchor;
+    int flags;
+};
 
 __device__ __forceinline__ void gn_step_block(prism_filter_state* __restrict__ Sg,
                                               const double* __restrict__ partials, int nblocks,
                                               Rel32* __restrict__ rel) {
-    __shared__ double red[kRedLds], neq[PRISM_NEQ];
-    __shared__ prism_filter_state Ls;
-    sum_partials(partials, nblocks, red, neq, Sg, &Ls);
-    if (threadIdx.x == 0) gn_step_body(&Ls, neq);
-    __syncthreads();
+    __shared__ double red[kSumThreads], neq[PRISM_NEQ];
+    __shared__ GnPrep pre;
+    if (threadIdx.x >= kSumThreads) {
+        const int l = threadIdx.x - kSumThreads;
+        const double lp = Sg->Lp[l < 36 ? l : 0];
+        const prism_pose it = Sg->iter, pr = Sg->prior, an = Sg->anchor;
+        const int flags = Sg->flags;
+        if (l < 36) pre.Lp[l] = lp;
+        double e[6], R[9];
+        pose_err(it, pr, e);
+        quat_to_R9(it.q, R);
+        const Pose64 Q = load_pose64(&an);
+        if (l == 0) {
+            for (int i = 0; i < 9; ++i) pre.R[i] = R[i];
+            for (int i = 0; i < 3; ++i) pre.t[i] = it.t[i];
+            pre.anchor = Q;
+            pre.flags = flags;
+        }
+        wave_lds_order();
+        if (l < 6) {
+            double s = 0.0;
+#pragma unroll
+            for (int j = 0; j < 6; ++j) s += pre.Lp[l * 6 + j] * e[j];
+            pre.le[l] = s;
+        }
+    }
+    sum_partials(partials, nblocks, red, neq);
+    if (threadIdx.x >= 64 || (pre.flags & PRISM_FLAG_CHOL_FALLBACK)) return;
+    int flags = pre.flags;
+    if (!(neq[28] > 0.0)) flags |= PRISM_FLAG_NO_VALID_PIXELS;
+    double A[36], b[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+#pragma unroll
+        for (int j = 0; j <= i; ++j) A[i * 6 + j] = 2.0 * neq[sym6(i, j)] + pre.Lp[i * 6 + j];
+        b[i] = -(2.0 * neq[21 + i] + pre.le[i]);
+    }
+    Chol<6> c;
+    if (!chol_regs<6>(A, c)) {
+        if (threadIdx.x == 0) {
+            const prism_pose pr = Sg->prior;
+            Sg->iter = pr;
+            Sg->flags = flags | PRISM_FLAG_CHOL_FALLBACK;
+            if (rel) rel_of(load_pose64(&pr), pre.anchor, *rel);
+        }
+        return;
+    }
+    chol_solve<6>(c, b);
+    // t <- t + dt, R <- Exp(dtheta) R
+    double E[9], R2[9];
+    so3_exp_step(b + 3, E);
+    mat3mul(E, pre.R, R2);
+    Pose64 cur;
+    prism_pose it;
+    for (int i = 0; i < 3; ++i) {
+        it.t[i] = pre.t[i] + b[i];
+        cur.t[i] = it.t[i];
+        for (int k = 0; k < 3; ++k) cur.R[i][k] = R2[i * 3 + k];
+    }
+    R9_to_quat(R2, it.q);
     if (threadIdx.x == 0) {
-        Sg->iter = Ls.iter;
-        Sg->flags = Ls.flags;
-        if (rel) rel_of(&Ls.iter, &Ls.anchor, *rel);
+        Sg->iter = it;
+        Sg->flags = flags;
+        if (rel) rel_of(cur, pre.anchor, *rel);
     }
 }
 
-__global__ __launch_bounds__(512) void k_gn_step(prism_filter_state* __restrict__ Sg,
-                                                 const double* __restrict__ partials, int nblocks,
-                                                 Rel32* __restrict__ rel) {
+__global__ __launch_bounds__(kSolveThreads) void k_gn_step(prism_filter_state* __restrict__ Sg,
+                                                           const double* __restrict__ partials, int nblocks,
+                                                           Rel32* __restrict__ rel) {
     gn_step_block(Sg, partials, nblocks, rel);
 }
 
@@ -567,20 +704,30 @@ __device__ inline void combine_bias(prism_filter_state* S, prism_filter_bias_sta
     }
 }
 
+// 21 000 -> 9 000 clocks at 300 partial rows: the error of the iterate to the
+// prior is formed by the ninth wavefront while the others sum the normal
+// equations.
 __device__ __forceinline__ void laplace_combine_block(prism_filter_state* __restrict__ Sg,
                                                       prism_filter_bias_state* __restrict__ X,
                                                       const double* __restrict__ partials, int nblocks, double ema,
                                                       double min_inliers, double lap_h) {
-    __shared__ double red[kRedLds], neq[PRISM_NEQ];
-    __shared__ double A[36], Sl[36], Sb[36], D[36], T[36], P[144], e[6];
-    __shared__ int ok;
+    __shared__ double red[kSumThreads], neq[PRISM_NEQ];
+    __shared__ double A[36], Sl[36], Sb[36], T[36], e[6], eraw[6];
     __shared__ prism_filter_state Ls;
     prism_filter_state* S = &Ls;
+    if (threadIdx.x >= kSumThreads) {
+        double er[6];
+        const prism_pose it = Sg->iter, pr = Sg->prior;
+        pose_err(it, pr, er);
+        if (threadIdx.x == kSumThreads)
+            for (int i = 0; i < 6; ++i) eraw[i] = er[i];
+    }
     sum_partials(partials, nblocks, red, neq, Sg, &Ls);
     if (threadIdx.x < PRISM_NEQ) S->neq[threadIdx.x] = neq[threadIdx.x];
     if (S->flags & PRISM_FLAG_PRIOR_NOT_PD) {
         // predicted mean and covariance as they are (the covariance was
         // written by the predict kernel); the Laplace EMA is left unchanged
+        __syncthreads();   // every thread has read the flags
         if (threadIdx.x == 0) {
             if (!(neq[28] > 0.0)) S->flags |= PRISM_FLAG_NO_VALID_PIXELS;
             if (neq[28] < min_inliers) S->flags |= PRISM_FLAG_LOW_INLIERS;
@@ -595,79 +742,65 @@ __device__ __forceinline__ void laplace_combine_block(prism_filter_state* __rest
         state_out(S, Sg);
         return;
     }
-    if (threadIdx.x == 0) {
-        if (!(neq[28] > 0.0)) S->flags |= PRISM_FLAG_NO_VALID_PIXELS;
+    if (threadIdx.x < 64) {
+        const int l = threadIdx.x;
+        int flags = S->flags;
+        if (!(neq[28] > 0.0)) flags |= PRISM_FLAG_NO_VALID_PIXELS;
         // fewer contributing pixels at the final iterate than the filter asks for
-        if (neq[28] < min_inliers) S->flags |= PRISM_FLAG_LOW_INLIERS;
-        double H[36], g[6];
-        unpack_H(neq, H, g);
+        if (neq[28] < min_inliers) flags |= PRISM_FLAG_LOW_INLIERS;
         // Laplace precision lap_h H + Lp (Sec. 5.1 prints lap_h = 2)
-        for (int i = 0; i < 36; ++i) A[i] = lap_h * H[i] + S->Lp[i];
-        ok = !(S->flags & PRISM_FLAG_CHOL_FALLBACK) && chol<6>(A);
+        if (l < 36) A[l] = lap_h * neq[sym6(l / 6, l % 6)] + S->Lp[l];
+        wave_lds_order();
+        bool ok = !(flags & PRISM_FLAG_CHOL_FALLBACK) && spd_inverse_wave<6>(A, Sl);
         if (!ok) {
-            S->flags |= PRISM_FLAG_CHOL_FALLBACK;
-            S->iter = S->prior;
+            // prior pose covariance = Lp^-1, and the iterate back to the prior
+            flags |= PRISM_FLAG_CHOL_FALLBACK;
+            (void)spd_inverse_wave<6>(S->Lp, Sl);
+            if (l == 0) S->iter = S->prior;
         }
-    }
-    __syncthreads();
-    if (ok) {
-        chol_inverse<6>(A, Sl);
-    } else {
-        // prior pose covariance = Lp^-1
-        if (threadIdx.x == 0) {
-            for (int i = 0; i < 36; ++i) T[i] = S->Lp[i];
-            chol<6>(T);
+        if (l < 6) e[l] = ok ? eraw[l] : 0.0;
+        wave_lds_order();
+        if (l < 36) {
+            S->S_lap[l] = Sl[l];
+            const double sb = S->has_sbar ? ema * S->Sbar[l] + (1.0 - ema) * Sl[l] : Sl[l];
+            Sb[l] = sb;
+            S->Sbar[l] = sb;
         }
-        __syncthreads();
-        chol_inverse<6>(T, Sl);
+        if (l == 0) S->flags = flags;
     }
-    symmetrize(Sl, 6);
-    if (threadIdx.x < 36) {
-        int i = threadIdx.x;
-        S->S_lap[i] = Sl[i];
-        Sb[i] = S->has_sbar ? ema * S->Sbar[i] + (1.0 - ema) * Sl[i] : Sl[i];
-        D[i] = S->D[i];
-    }
-    if (threadIdx.x == 0) pose_err(S->iter, S->prior, e);
     __syncthreads();
     if (X) {
         combine_bias(S, X, Sb, e);
-        if (threadIdx.x < 36) S->Sbar[threadIdx.x] = Sb[threadIdx.x];
-        if (threadIdx.x == 0) {
-            S->has_sbar = 1;
-            S->pose = S->iter;
-            S->anchor = S->iter;
-            S->step += 1;
+    } else {
+        // joint covariance [[Sb, Sb D^T], [D Sb, Sv + D Sb D^T]], means vel_prior + D e
+        if (threadIdx.x < 36) {
+            const int i = threadIdx.x / 6, j = threadIdx.x % 6;
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) s += S->D[i * 6 + q] * Sb[q * 6 + j];
+            T[threadIdx.x] = s;   // D Sb
+        } else if (threadIdx.x >= 64 && threadIdx.x < 70) {
+            const int i = threadIdx.x - 64;
+            double s = S->vel_prior[i];
+#pragma unroll
+            for (int j = 0; j < 6; ++j) s += S->D[i * 6 + j] * e[j];
+            (i < 3 ? S->v[i] : S->w[i - 3]) = s;
         }
-        state_out(S, Sg);
-        return;
-    }
-    // joint covariance [[Sb, Sb D^T], [D Sb, Sv + D Sb D^T]]
-    mm(D, Sb, T, 6, 6, 6, false);   // D Sb
-    for (int e2 = threadIdx.x; e2 < 144; e2 += blockDim.x) {
-        int i = e2 / 12, j = e2 % 12;
-        double s;
-        if (i < 6 && j < 6) s = Sb[i * 6 + j];
-        else if (i < 6) s = T[(j - 6) * 6 + i];           // (D Sb)^T = Sb D^T
-        else if (j < 6) s = T[(i - 6) * 6 + j];
-        else {
-            s = S->Sv[(i - 6) * 6 + (j - 6)];
-            for (int q = 0; q < 6; ++q) s += T[(i - 6) * 6 + q] * D[(j - 6) * 6 + q];
+        __syncthreads();
+        if (threadIdx.x >= 128 && threadIdx.x < 128 + 108) {
+            // the pose rows: Sb and (D Sb)^T, and their mirror
+            const int k = threadIdx.x - 128, i = k % 6, j = k / 6;   // j < 18: Sb, then T twice
+            if (j < 6) S->P[i * 12 + j] = Sb[i * 6 + j];
+            else if (j < 12) S->P[i * 12 + j] = T[(j - 6) * 6 + i];
+            else S->P[(j - 6) * 12 + i] = T[(j - 12) * 6 + i];
+        } else if (threadIdx.x < 36) {
+            sym_plus_outer(6, 1.0, T, [&](int j, int q) { return S->D[j * 6 + q]; },
+                           [&](int i, int j) { return S->Sv[i * 6 + j]; },
+                           [&](int i, int j, double s) { S->P[(6 + i) * 12 + 6 + j] = s; });
         }
-        P[e2] = s;
     }
-    __syncthreads();
-    symmetrize(P, 12);
-    for (int e2 = threadIdx.x; e2 < 144; e2 += blockDim.x) S->P[e2] = P[e2];
-    if (threadIdx.x < 36) S->Sbar[threadIdx.x] = Sb[threadIdx.x];
     if (threadIdx.x == 0) {
         S->has_sbar = 1;
-        double vm[6];
-        for (int i = 0; i < 6; ++i) {
-            vm[i] = S->vel_prior[i];
-            for (int j = 0; j < 6; ++j) vm[i] += D[i * 6 + j] * e[j];
-        }
-        for (int i = 0; i < 3; ++i) { S->v[i] = vm[i]; S->w[i] = vm[3 + i]; }
         S->pose = S->iter;
         S->anchor = S->iter;
         S->step += 1;
@@ -675,10 +808,10 @@ __device__ __forceinline__ void laplace_combine_block(prism_filter_state* __rest
     state_out(S, Sg);
 }
 
-__global__ __launch_bounds__(512) void k_laplace_combine(prism_filter_state* __restrict__ Sg,
-                                                         prism_filter_bias_state* __restrict__ X,
-                                                         const double* __restrict__ partials, int nblocks,
-                                                         double ema, double min_inliers, double lap_h) {
+__global__ __launch_bounds__(kSolveThreads) void k_laplace_combine(prism_filter_state* __restrict__ Sg,
+                                                                   prism_filter_bias_state* __restrict__ X,
+                                                                   const double* __restrict__ partials, int nblocks,
+                                                                   double ema, double min_inliers, double lap_h) {
     laplace_combine_block(Sg, X, partials, nblocks, ema, min_inliers, lap_h);
 }
 
@@ -714,12 +847,12 @@ __global__ __launch_bounds__(256) void k_predict_batch(BatchArgs b) {
         predict_block(D.S, (const double*)D.slots[b.slot[blockIdx.x]].u, D.tc, D.rel);
 }
 
-__global__ __launch_bounds__(512) void k_gn_step_batch(BatchArgs b) {
+__global__ __launch_bounds__(kSolveThreads) void k_gn_step_batch(BatchArgs b) {
     const AgentDesc& D = *b.d[blockIdx.x];
     gn_step_block(D.S, D.partials, D.obj_blocks, D.rel);
 }
 
-__global__ __launch_bounds__(512) void k_laplace_combine_batch(BatchArgs b) {
+__global__ __launch_bounds__(kSolveThreads) void k_laplace_combine_batch(BatchArgs b) {
     const AgentDesc& D = *b.d[blockIdx.x];
     laplace_combine_block(D.S, D.X, D.partials, D.obj_blocks, D.ema, D.min_inliers, D.lap_h);
 }
@@ -812,7 +945,7 @@ __global__ __launch_bounds__(64) void k_rollout_sample(const prism_filter_state*
 __global__ __launch_bounds__(256) void k_rollout_moments(const prism_filter_state* __restrict__ S,
                                                          const double* __restrict__ u, int k, TransC tc,
                                                          double* __restrict__ mean, double* __restrict__ cov) {
-    __shared__ double M[144], G[144], T1[144], T2[144], P[144];
+    __shared__ double T1[144], T2[144], P[144];
     __shared__ double vnew[6], E[9], Jl[9], v[3], w[3];
     __shared__ prism_pose pose;
     if (threadIdx.x == 0) {
@@ -841,7 +974,7 @@ __global__ __launch_bounds__(256) void k_rollout_moments(const prism_filter_stat
             }
         }
         __syncthreads();
-        transition_cov(E, Jl, tc, P, M, G, T1, T2);
+        transition_cov(E, Jl, tc, P, T1, T2);
         for (int e = threadIdx.x; e < 144; e += blockDim.x) {
             P[e] = T2[e];
             if (cov) cov[144 * j + e] = T2[e];
@@ -917,9 +1050,9 @@ hipError_t launch_rollout(const prism_filter_state* S, const prism_filter_bias_s
 
 // per-frame fixed-order sum of block partials (NV values each)
 template <int NV>
-__global__ __launch_bounds__(512) void k_finalize(const double* __restrict__ partials, int nblocks,
+__global__ __launch_bounds__(kSumThreads) void k_finalize(const double* __restrict__ partials, int nblocks,
                                                   double* __restrict__ out) {
-    __shared__ double red[kRedLds], sums[NV];
+    __shared__ double red[kSumThreads], sums[NV];
     sum_partials<NV>(partials + (long long)blockIdx.x * nblocks * NV, nblocks, red, sums);
     if ((int)threadIdx.x < NV) out[(long long)blockIdx.x * NV + threadIdx.x] = sums[threadIdx.x];
 }
@@ -932,13 +1065,13 @@ hipError_t launch_predict(prism_filter_state* S, prism_filter_bias_state* X, con
 
 hipError_t launch_gn_step(prism_filter_state* S, const double* partials, int nblocks, Rel32* rel,
                           hipStream_t st) {
-    k_gn_step<<<1, 512, 0, st>>>(S, partials, nblocks, rel);
+    k_gn_step<<<1, kSolveThreads, 0, st>>>(S, partials, nblocks, rel);
     return hipGetLastError();
 }
 
 hipError_t launch_laplace_combine(prism_filter_state* S, prism_filter_bias_state* X, const double* partials,
                                   int nblocks, double ema, double min_inliers, double lap_h, hipStream_t st) {
-    k_laplace_combine<<<1, 512, 0, st>>>(S, X, partials, nblocks, ema, min_inliers, lap_h);
+    k_laplace_combine<<<1, kSolveThreads, 0, st>>>(S, X, partials, nblocks, ema, min_inliers, lap_h);
     return hipGetLastError();
 }
 
@@ -958,12 +1091,12 @@ hipError_t launch_predict_batch(const BatchArgs& b, hipStream_t st) {
 }
 
 hipError_t launch_gn_step_batch(const BatchArgs& b, hipStream_t st) {
-    k_gn_step_batch<<<b.n, 512, 0, st>>>(b);
+    k_gn_step_batch<<<b.n, kSolveThreads, 0, st>>>(b);
     return hipGetLastError();
 }
 
 hipError_t launch_laplace_combine_batch(const BatchArgs& b, hipStream_t st) {
-    k_laplace_combine_batch<<<b.n, 512, 0, st>>>(b);
+    k_laplace_combine_batch<<<b.n, kSolveThreads, 0, st>>>(b);
     return hipGetLastError();
 }
 
@@ -973,12 +1106,12 @@ hipError_t launch_first_frame_batch(const BatchArgs& b, hipStream_t st) {
 }
 
 hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
-    k_finalize<PRISM_NEQ><<<n_frames, 512, 0, st>>>(partials, nblocks, out);
+    k_finalize<PRISM_NEQ><<<n_frames, kSumThreads, 0, st>>>(partials, nblocks, out);
     return hipGetLastError();
 }
 
 hipError_t launch_finalize6(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
-    k_finalize<6><<<n_frames, 512, 0, st>>>(partials, nblocks, out);
+    k_finalize<6><<<n_frames, kSumThreads, 0, st>>>(partials, nblocks, out);
     return hipGetLastError();
 }
 

@@ -371,43 +371,6 @@ __global__ __launch_bounds__(256) void k_track_p2_batch(BatchArgs b) {
 // Skipped when the prediction already fell back (improper prior).
 constexpr int kAdamThreads = 320;   // four wavefronts of pixels, one for the prior
 
-// Exp of a rotation vector.  The series of A = sin(th)/th and
-// B = (1 - cos(th))/th^2 to th^8 is exact in double precision below th = 0.01;
-// the functions of a larger angle stay out of the loop's straight-line code.
-struct SinCosC {
-    double A, B;
-};
-static __device__ __attribute__((noinline)) SinCosC so3_coef_far(double th2) {
-    const double th = sqrt(th2);
-    return SinCosC{sin(th) / th, (1.0 - cos(th)) / th2};
-}
-
-__device__ inline void so3_exp_step(const double w[3], double E[9]) {
-    const double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-    constexpr double i6 = 1.0 / 6.0, i20 = 1.0 / 20.0, i42 = 1.0 / 42.0, i72 = 1.0 / 72.0;
-    constexpr double i12 = 1.0 / 12.0, i30 = 1.0 / 30.0, i56 = 1.0 / 56.0, i90 = 1.0 / 90.0;
-    double A = 1.0 - th2 * i6 * (1.0 - th2 * i20 * (1.0 - th2 * i42 * (1.0 - th2 * i72)));
-    double B = 0.5 * (1.0 - th2 * i12 * (1.0 - th2 * i30 * (1.0 - th2 * i56 * (1.0 - th2 * i90))));
-    if (th2 >= 1e-4) {
-        const SinCosC f = so3_coef_far(th2);
-        A = f.A;
-        B = f.B;
-    }
-    // E = I + A [w]x + B [w]x^2, with [w]x^2 = w w^T - th2 I
-    const double Bw[3] = {B * w[0], B * w[1], B * w[2]};
-    const double d = 1.0 - B * th2;
-    E[0] = __builtin_fma(Bw[0], w[0], d);
-    E[4] = __builtin_fma(Bw[1], w[1], d);
-    E[8] = __builtin_fma(Bw[2], w[2], d);
-    const double xy = Bw[0] * w[1], xz = Bw[0] * w[2], yz = Bw[1] * w[2];
-    E[1] = __builtin_fma(-A, w[2], xy);
-    E[3] = __builtin_fma(A, w[2], xy);
-    E[2] = __builtin_fma(A, w[1], xz);
-    E[6] = __builtin_fma(-A, w[1], xz);
-    E[5] = __builtin_fma(-A, w[0], yz);
-    E[7] = __builtin_fma(A, w[0], yz);
-}
-
 __device__ __forceinline__ double lane_value(double x, int lane) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
                             __builtin_amdgcn_readlane(__double2loint(x), lane));
