@@ -177,25 +177,74 @@ __device__ __forceinline__ double p2_colour_rows(const CamC& c, const CamD& cd, 
     return l1;
 }
 
+// Every anchor value of a pixel loaded at once, before the masks are known and
+// without a branch: one memory round trip, covered by the arithmetic that does
+// not need the anchor (left inside branches the compiler sinks each load into
+// the one that uses it).  Pixels without an association read pixel 0.
+struct EagerTaps {
+    AnchorTaps tap;
+    int m[6];   // mask and normal mask of the nearest pixel, masks of the corners
+};
+
+__device__ __forceinline__ EagerTaps load_taps(const CamC& c, const Assoc& as, const float* __restrict__ a_depth,
+                                               const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
+                                               const float* __restrict__ a_normals,
+                                               const uint8_t* __restrict__ a_nmask) {
+    EagerTaps o;
+    const int dx = as.pho ? 1 : 0, dy = as.pho ? c.W : 0;
+    o.m[0] = a_mask[as.q];
+    o.m[1] = a_nmask[as.q];
+    o.m[2] = a_mask[as.q00];
+    o.m[3] = a_mask[as.q00 + dx];
+    o.m[4] = a_mask[as.q00 + dy];
+    o.m[5] = a_mask[as.q00 + dy + dx];
+    o.tap.depth = a_depth[as.q];
+    const float3u n = *reinterpret_cast<const float3u*>(a_normals + 3 * as.q);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) o.tap.n[a] = n[a];
+    load_corners(a_rgb, as.q00, dx, dy, o.tap);
+    return o;
+}
+
 // The rows of an observed pixel (column u, row v): geometric row 0 and colour
 // rows 1-3, residuals in double precision, Jacobians in single precision.
 // rm: bit 0 the geometric row passed its gate, bit 1 the colour rows.
 // D and orgb: the pixel's observed depth and colour (loaded by the caller).
-// Masks first, then the anchor values they admit: fewest loads and registers,
-// for a GPU full of wavefronts.
+// Eager: the anchor by load_taps, for launches that leave the GPU waiting;
+// otherwise masks first, then the values they admit (fewest loads and
+// registers), for a GPU full of wavefronts, which is bound by issue.
+template <bool Eager>
 __device__ __forceinline__ void p2_pixel(const CamC& c, const CamD& cd, const Rel32& rel, int u, int v, float D,
                                          const float orgb[3], const float* __restrict__ a_depth,
                                          const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
                                          const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
                                          const WeightsC& wt, float J[4][6], double r[4], int& rm) {
+    rm = 0;
+    const Assoc as = p2_assoc(c, rel, u, v, D);
+    if constexpr (Eager) {
+        const EagerTaps e = load_taps(c, as, a_depth, a_rgb, a_mask, a_normals, a_nmask);
+        const Moved m = p2_moved(cd, rel, u, v, D);
+        p2_geo_row(cd, m, as, e.tap, J[0], r[0]);
+        const double l1 = p2_colour_rows(c, cd, m, as, e.tap, orgb, J + 1, r + 1);
+        const bool geo = as.geo & (e.m[0] != 0) & (e.m[1] != 0);
+        const bool pho = as.pho & (e.m[2] != 0) & (e.m[3] != 0) & (e.m[4] != 0) & (e.m[5] != 0);
+        if (geo && fabs(r[0]) <= wt.gate_depth) rm |= 1;
+        if (pho && l1 <= wt.gate_rgb) rm |= 2;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const bool keep = a ? pho : geo;
+            r[a] = keep ? r[a] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) J[a][q] = keep ? J[a][q] : 0.0f;
+        }
+        return;
+    }
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         r[a] = 0.0;
 #pragma unroll
         for (int m = 0; m < 6; ++m) J[a][m] = 0.0f;
     }
-    rm = 0;
-    const Assoc as = p2_assoc(c, rel, u, v, D);
     const bool geo = as.geo && a_mask[as.q] && a_nmask[as.q];
     const bool pho = as.pho && a_mask[as.q00] && a_mask[as.q00 + 1] && a_mask[as.q00 + c.W] && a_mask[as.q00 + c.W + 1];
     if (!(geo || pho)) return;
@@ -214,32 +263,21 @@ __device__ __forceinline__ void p2_pixel(const CamC& c, const CamD& cd, const Re
     }
 }
 
-// The pixel's share of the gradient sum w r J, added to g, with every anchor
-// value loaded at once and no branch: one memory round trip, covered by the
-// arithmetic that does not need the anchor (for a wavefront that has nothing
-// else to run meanwhile).  Pixels without an association read pixel 0.
+// The pixel's share of the gradient sum w r J, added to g
 __device__ __forceinline__ void p2_grad(const CamC& c, const CamD& cd, const Rel32& rel, int u, int v, float D,
                                         const float orgb[3], const float* __restrict__ a_depth,
                                         const float* __restrict__ a_rgb, const uint8_t* __restrict__ a_mask,
                                         const float* __restrict__ a_normals, const uint8_t* __restrict__ a_nmask,
                                         const WeightsC& wt, double g[6]) {
-    const Assoc as = p2_assoc(c, rel, u, v, D);
-    const int dx = as.pho ? 1 : 0, dy = as.pho ? c.W : 0;
-    const int m0 = a_mask[as.q], m1 = a_nmask[as.q], m2 = a_mask[as.q00], m3 = a_mask[as.q00 + dx],
-              m4 = a_mask[as.q00 + dy], m5 = a_mask[as.q00 + dy + dx];
-    AnchorTaps tap;
-    tap.depth = a_depth[as.q];
-    const float3u n = *reinterpret_cast<const float3u*>(a_normals + 3 * as.q);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) tap.n[a] = n[a];
-    load_corners(a_rgb, as.q00, dx, dy, tap);
-    const Moved m = p2_moved(cd, rel, u, v, D);
     float J[4][6];
     double r[4];
-    p2_geo_row(cd, m, as, tap, J[0], r[0]);
-    const double l1 = p2_colour_rows(c, cd, m, as, tap, orgb, J + 1, r + 1);
-    const bool geo = as.geo & (m0 != 0) & (m1 != 0) & (fabs(r[0]) <= wt.gate_depth);
-    const bool pho = as.pho & (m2 != 0) & (m3 != 0) & (m4 != 0) & (m5 != 0) & (l1 <= wt.gate_rgb);
+    const Assoc as = p2_assoc(c, rel, u, v, D);
+    const EagerTaps e = load_taps(c, as, a_depth, a_rgb, a_mask, a_normals, a_nmask);
+    const Moved m = p2_moved(cd, rel, u, v, D);
+    p2_geo_row(cd, m, as, e.tap, J[0], r[0]);
+    const double l1 = p2_colour_rows(c, cd, m, as, e.tap, orgb, J + 1, r + 1);
+    const bool geo = as.geo & (e.m[0] != 0) & (e.m[1] != 0) & (fabs(r[0]) <= wt.gate_depth);
+    const bool pho = as.pho & (e.m[2] != 0) & (e.m[3] != 0) & (e.m[4] != 0) & (e.m[5] != 0) & (l1 <= wt.gate_rgb);
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
         const double ag = wt.w_depth * r[0] * (double)J[0][q];
@@ -252,6 +290,7 @@ __device__ __forceinline__ void p2_grad(const CamC& c, const CamD& cd, const Rel
 
 // one workgroup (blk: its index within this frame's grid) of the tracking
 // objective; partials receives the workgroup's 29 sums at row blk
+template <bool Eager>
 __device__ __forceinline__ void track_p2_block(int blk, const CamC& c, const CamD& cd,
                                                const prism_pose* __restrict__ pose,
                                                const prism_pose* __restrict__ pose_prev,
@@ -293,7 +332,7 @@ __device__ __forceinline__ void track_p2_block(int blk, const CamC& c, const Cam
         int u, v;
         pixel_uv(c.W, p, u, v);
         const float orgb[3] = {obs_rgb[3 * p], obs_rgb[3 * p + 1], obs_rgb[3 * p + 2]};
-        p2_pixel(c, cd, rel, u, v, obs_depth[p], orgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, wt, J, r, rm);
+        p2_pixel<Eager>(c, cd, rel, u, v, obs_depth[p], orgb, a_depth, a_rgb, a_mask, a_normals, a_nmask, wt, J, r, rm);
         if (rm & 1) neq_add32(pacc, J[0], (float)r[0], row_weight(wt, false, r[0]));
         if (rm & 2)
 #pragma unroll
@@ -313,6 +352,7 @@ __device__ __forceinline__ void track_p2_block(int blk, const CamC& c, const Cam
     block_reduce29f(pacc, lds, partials + (long long)blk * PRISM_NEQ);
 }
 
+template <bool Eager>
 __global__ __launch_bounds__(256) void k_track_p2(CamC c, CamD cd, const prism_pose* __restrict__ pose,
                                                   const prism_pose* __restrict__ pose_prev,
                                                   const float* __restrict__ obs_depth,
@@ -325,7 +365,7 @@ __global__ __launch_bounds__(256) void k_track_p2(CamC c, CamD cd, const prism_p
                                                   float* __restrict__ Jout, float* __restrict__ resid,
                                                   uint8_t* __restrict__ rowmask,
                                                   double* __restrict__ partials, const Rel32* __restrict__ rel) {
-    track_p2_block(blockIdx.x, c, cd, pose, pose_prev, obs_depth, obs_rgb, a_depth, a_rgb, a_mask, a_normals, a_nmask,
+    track_p2_block<Eager>(blockIdx.x, c, cd, pose, pose_prev, obs_depth, obs_rgb, a_depth, a_rgb, a_mask, a_normals, a_nmask,
                    wt, Jout, resid, rowmask, partials, rel);
 }
 
@@ -335,7 +375,7 @@ __global__ __launch_bounds__(256) void k_track_p2_batch(BatchArgs b) {
     const int a = batch_agent(b, blockIdx.x);
     const AgentDesc& D = *b.d[a];
     const prism_frame& fr = D.slots[b.slot[a]];
-    track_p2_block(blockIdx.x - b.start[a], D.c, D.cd, &D.S->iter, &D.S->anchor, (const float*)fr.depth,
+    track_p2_block<false>(blockIdx.x - b.start[a], D.c, D.cd, &D.S->iter, &D.S->anchor, (const float*)fr.depth,
                    (const float*)fr.rgb, D.a_depth, D.a_rgb, D.a_mask, D.a_normals, D.a_nmask, b.irls ? D.w_irls : D.w,
                    nullptr, nullptr, nullptr, D.partials, D.rel);
 }
@@ -553,8 +593,13 @@ hipError_t launch_track_p2(const CamC& c, const CamD& cd, const prism_pose* pose
                            const float* a_rgb, const uint8_t* a_mask, const float* a_normals,
                            const uint8_t* a_nmask, const WeightsC& w, float* J, float* resid,
                            uint8_t* rowmask, double* partials, const Rel32* rel, hipStream_t st) {
-    k_track_p2<<<track_blocks(c), 256, 0, st>>>(c, cd, pose, pose_prev, obs_depth, obs_rgb, a_depth, a_rgb,
-                                                a_mask, a_normals, a_nmask, w, J, resid, rowmask, partials, rel);
+    // A lone frame leaves the GPU waiting on a chain of loads (320x240: 1.2
+    // wavefronts per SIMD; 7.0 us masks first, 6.0 eager; 160x120 6.5 / 5.8;
+    // 640x480, 4.7 per SIMD, 9.7 / 9.45); from six wavefronts per SIMD, as many
+    // as the other variant's registers admit, loads wait for their masks.
+    auto* k = track_blocks(c) <= 1536 ? k_track_p2<true> : k_track_p2<false>;
+    k<<<track_blocks(c), 256, 0, st>>>(c, cd, pose, pose_prev, obs_depth, obs_rgb, a_depth, a_rgb, a_mask, a_normals,
+                                       a_nmask, w, J, resid, rowmask, partials, rel);
     return hipGetLastError();
 }
 

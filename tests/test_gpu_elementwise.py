@@ -173,6 +173,36 @@ def test_track_p2_per_element(small, big, size):
     neq_check(out["neq"][0].cpu().numpy(), ref["neq"], f"P2 {size}")
 
 
+@pytest.mark.parametrize("width,height", [(1, 1), (9, 1), (257, 3), (640, 614), (641, 615)])
+def test_track_p2_sizes(width, height):
+    """Images at the edges of the tracking kernel: one pixel or row (no
+    bilinear neighbours), a partly filled workgroup, and either side of the
+    workgroup count from which anchor values are no longer loaded ahead of
+    their masks.  Rows and sums as in the test above."""
+    banner(f"track_p2 {width}x{height}")
+    c = synth.trajectory_case(seed=6, n=64, width=width, height=height, n_samples=32, n_frames=1, frames=False)
+    mean = synth.gt_map(c["scene"])[0].astype(np.float32).astype(np.float64)
+    rng = np.random.default_rng(4)
+    prev = synth.pose7(c["traj"].t[0], c["traj"].q[0])
+    a64, adev, od, oc, cur = _p2_case(c, mean, prev, rng)
+    od.ravel()[::37] = 0.0
+    out = P().track_p2(cam_of(c["cam"]), P().poses_tensor(cur), P().poses_tensor(prev), t(od), t(oc), adev,
+                       P().Weights.make(), want_J=True, want_resid=True)
+    ref = orc.track_p2(orc.cam_from(c["cam"]), cur, prev, od, oc, a64, orc.Params(), want_J=True)
+    rm = out["rowmask"].cpu().numpy()
+    np.testing.assert_array_equal(rm, ref["rowmask"], err_msg="P2 row masks")
+    use = rm > 0
+    assert use.sum() > 1000 or width * height < 1000
+    J, r = out["J"].cpu().numpy(), out["resid"].cpu().numpy()
+    assert not J[~use & (od <= 0)].any() and not r[~use & (od <= 0)].any()
+    if use.any():
+        rows_check(J[use], ref["J"][use], f"P2 {width}x{height}")
+        assert np.all(np.abs(r[use] - ref["resid"][use]) <= 1e-6 * np.maximum(np.abs(ref["resid"][use]), 1.0))
+        neq_check(out["neq"][0].cpu().numpy(), ref["neq"], f"P2 {width}x{height}")
+    else:
+        assert not out["neq"].any()
+
+
 # ---------------------------------------------------------------------------
 # anchor normals
 # ---------------------------------------------------------------------------
