@@ -212,24 +212,26 @@ def _check(status: int):
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    return ctypes.c_void_p(t.data_ptr())
+    # a plain integer: every entry's argtypes turn it into a pointer
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    # the current stream's handle without a torch.cuda.Stream around it: that
+    # object was 2.7 us of a 17 us tracking call's time on the host
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
-def _dev(t: torch.Tensor, dtype: torch.dtype, name: str, shape: Optional[Sequence[int]] = None) -> torch.Tensor:
+def _dev(t: torch.Tensor, dtype: torch.dtype, name: str, shape: Optional[tuple] = None) -> torch.Tensor:
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise PrismError(f"{name} must be a CUDA tensor")
     if t.dtype != dtype:
         raise PrismError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise PrismError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise PrismError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
