@@ -16,6 +16,7 @@
 // The adjoint takes four lanes per ray as well (8x8 pixels per workgroup):
 // from the given hit index it recomputes the two samples, nothing to march,
 // and lane s scatters the gradient of plane s.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -810,10 +811,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // the window.  Measured at 256^3, 320x240 (hash tables per tile before): the
 // adjoint of 8 frames 399 -> 113 us (67 without any scatter), the descent
 // gradient 72 -> 40 us (23).
-constexpr int kWin = 256;   // voxels per plane; a box of as many spans fewer than 64 bricks
 
 template <typename V, int Copies>
 struct Scatter {
+    // voxels per plane; a box of as many spans fewer than 64 bricks.  Double
+    // windows are what lets a fifth workgroup onto a CU (32000 bytes each, with
+    // the free-space bits, done with by then, in the same LDS): a 320x240 frame's
+    // 1200 tiles are then all resident at once; the descent gradient takes 37 us
+    // with 256 (four per CU), 34 with 236.
+    static constexpr int kWin = sizeof(V) == 8 ? 236 : 256;
     V win[4][Copies][kWin + 8];   // planes and copies shifted in the banks
 };
 
@@ -828,7 +834,7 @@ template <typename V, int Copies>
 struct TileScatter {
     Scatter<V, Copies> wave[4];
     Window at[4];
-    int mark[256];   // bricks of a box that goes out (of each window's 64, when they go out one by one)
+    uint8_t mark[256];   // bricks of a box that goes out (of each window's 64, when they go out one by one)
 };
 
 // pixels of a scattering wavefront: 4x4, four wavefronts per 8x8 tile
@@ -871,7 +877,7 @@ __device__ __forceinline__ Window scatter_window(const GridC& g, Scatter<V, Copi
     w.dy = hi[1] - lo[1] + 1;
     w.dz = hi[2] - lo[2] + 1;
     w.vol = w.dx * w.dy * w.dz;   // at most 2^30
-    if (w.vol > kWin) {
+    if (w.vol > Scatter<V, Copies>::kWin) {
         w.vol = -1;
         return w;
     }
@@ -992,7 +998,7 @@ __device__ __forceinline__ void scatter_flush(const GridC& g, TileScatter<V, Cop
         hi[2] = max(hi[2], w[k].z0 + w[k].dz - 1);
     }
     if (hi[0] < 0) return;
-    auto box = [&](int first, int step, const int lo[3], const int hi[3], int k0, int k1, int* mark, auto&& order) {
+    auto box = [&](int first, int step, const int lo[3], const int hi[3], int k0, int k1, uint8_t* mark, auto&& order) {
         const int gx0 = lo[0] >> 3, dy = hi[1] - lo[1] + 1, dz = hi[2] - lo[2] + 1;
         const int ngx = (hi[0] >> 3) - gx0 + 1, vol = ngx * 8 * dy * dz;
         constexpr bool marks = !std::is_same<Touched, NoMarks>::value;
@@ -1137,7 +1143,7 @@ __device__ __forceinline__ void mark_brick(unsigned* __restrict__ marks, int* __
     }
 }
 
-using GdScatter = TileScatter<double, 1>;    // 33 KB
+using GdScatter = TileScatter<double, 1>;    // 31.6 KB
 
 // One frame's rows of the map-filter objective at the current means: the
 // render-through rows (same validity, gates and weights as the P1 objective)
@@ -1155,8 +1161,8 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
                                                  int* __restrict__ list, double* __restrict__ partials) {
     __shared__ BlockPose sp;
     __shared__ double wsum[4];
-    __shared__ GdScatter T;
-    extern __shared__ __align__(16) unsigned lbits[];
+    extern __shared__ __align__(16) unsigned lbits[];   // the bits, then (every ray marched) the windows
+    GdScatter& T = *reinterpret_cast<GdScatter*>(lbits);
     lds_u32* const fb = block_setup(g, gbits, lbits, pose, &sp);   // synchronises the workgroup
     const BlockPose& P = sp;
     __shared__ int starts[4];
@@ -1168,17 +1174,18 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
     Cell c0{}, c1{};
     float w0[3] = {0.0f, 0.0f, 0.0f}, w1[3] = {0.0f, 0.0f, 0.0f};
     if (u < c.W && v < c.H) {
+        // the observation is in flight during the march
+        const int pix = v * c.W + u;
+        const float D = obs_depth[pix], O = s == 0 ? D : obs_rgb[3 * pix + s - 1];
         float dir[3];
         ray_dir32(c, P.f, u, v, dir);
         const RayCoef rc = ray_coef(g, c, P.f, dir);
         const int k = march_quad<float, false>(g, c, rc, map, fb, s, start);
-        const long long pix = (long long)v * c.W + u;
-        const float D = obs_depth[pix];
         if (k >= 1 && depth_ok(D)) {   // the same for the four lanes of a ray
             c0 = sample_cell(rc, k - 1);
             c1 = sample_cell(rc, k);
             const QuadShade q = shade_quad<float, false>(g, gd, cd, P.d, u, v, map, c0, c1, k, s);
-            const double r = s == 0 ? q.value - (double)D : q.value - (double)obs_rgb[3 * pix + s - 1];
+            const double r = q.value - (double)O;
             double l1 = s == 0 ? 0.0 : fabs(r);
             l1 = quad_sum(l1);
             const bool use_depth = fabs(quad_bcast0(r)) <= wt.gate_depth;
@@ -1323,8 +1330,9 @@ hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const 
                           const unsigned* bits, const prism_pose* pose, const float* obs_depth, const float* obs_rgb,
                           const WeightsC& w, double* grad, unsigned* marks, int* list, double* partials,
                           hipStream_t st) {
-    k_gd_grad<<<render_blocks(c), 256, bits_lds(g, bits), st>>>(g, c, gd, cd, map, bits, pose, obs_depth, obs_rgb, w,
-                                                                grad, marks, list, partials);
+    const size_t lds = std::max(bits_lds(g, bits), sizeof(GdScatter));
+    k_gd_grad<<<render_blocks(c), 256, lds, st>>>(g, c, gd, cd, map, bits, pose, obs_depth, obs_rgb, w, grad, marks,
+                                                  list, partials);
     return hipGetLastError();
 }
 
