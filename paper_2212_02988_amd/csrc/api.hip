@@ -896,10 +896,11 @@ prism_status prism_map_gd(const prism_grid* grid, void* map, const prism_camera*
     HIP_TRY(launch_gd_clear(marks, (int)((L.list - L.marks) / 4) + 1, stream));
     for (int it = 0; it < n_iters; ++it) {
         HIP_TRY(launch_gd_grad(g, c, gd, cd, (const float*)map, bits, pose, obs_depth, obs_rgb, wc, grad, marks, list,
-                               pd, stream));
-        HIP_TRY(launch_gd_update(g, (float*)map, aux, save, grad, list, saved, lr_occ, lr_rgb, pp, pd,
-                                 render_blocks(c), cost ? cost + it : nullptr, stream));
+                               pd, pp, cost && it > 0 ? cost + it - 1 : nullptr, stream));
+        HIP_TRY(launch_gd_update(g, (float*)map, aux, save, grad, list, saved, lr_occ, lr_rgb, pd, render_blocks(c),
+                                 pp, stream));
     }
+    HIP_TRY(launch_gd_end(g, aux, pp, cost ? cost + n_iters - 1 : nullptr, stream));
     return PRISM_OK;
 }
 

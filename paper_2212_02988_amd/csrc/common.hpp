@@ -467,6 +467,18 @@ __device__ __forceinline__ void wave_lds_order() {
 
 constexpr int kRedLds = 32 * 16;   // doubles of LDS scratch for block_reduce29
 
+// Descent: the objective before a step, from the step's per-workgroup
+// partials, by a workgroup of 256 threads in a fixed order (part: 4 doubles).
+__device__ inline void gd_cost_block(const double* __restrict__ pp, int np, double* __restrict__ cost, double* part) {
+    double a = 0.0;
+    for (int i = threadIdx.x; i < np; i += 256) a += pp[i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+    __syncthreads();
+    if (threadIdx.x == 0) *cost = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
 // Reduce a per-thread 29-vector over the block (blockDim.x a multiple of 64,
 // <= 1024) into out[0..28] (written by threads 0..28).  lds: kRedLds doubles.
 //

@@ -156,10 +156,12 @@ int map_update_groups_batch(const GridC& g);
 hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const CamD& cd, const float* map,
                           const unsigned* bits, const prism_pose* pose, const float* obs_depth, const float* obs_rgb,
                           const WeightsC& w, double* grad, unsigned* marks, int* list, double* partials,
-                          hipStream_t st);
+                          const double* pp, double* last_cost, hipStream_t st);
 hipError_t launch_gd_update(const GridC& g, float* map, const MapAux& aux, float* save, double* grad,
-                            const int* list, unsigned* saved, double lr_occ, double lr_rgb, double* partials,
-                            const double* pd, int nd, double* cost, hipStream_t st);
+                            const int* list, unsigned* saved, double lr_occ, double lr_rgb, const double* pd, int nd,
+                            double* partials, hipStream_t st);
+// after a run's last step: the dilated bits, and cost (if given) from its partials
+hipError_t launch_gd_end(const GridC& g, const MapAux& aux, const double* pp, double* cost, hipStream_t st);
 hipError_t launch_gd_clear(unsigned* words, int n, hipStream_t st);
 int gd_update_groups(const GridC& g);
 

@@ -810,7 +810,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // the four lanes of a ray have a plane each, and no other wavefront shares
 // the window.  Measured at 256^3, 320x240 (hash tables per tile before): the
 // adjoint of 8 frames 399 -> 113 us (67 without any scatter), the descent
-// gradient 72 -> 40 us (23).
+// gradient 72 -> 40 us (23; 34 with five workgroups per CU, see Scatter).
 
 template <typename V, int Copies>
 struct Scatter {
@@ -1158,9 +1158,16 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
                                                  const float* __restrict__ obs_depth,
                                                  const float* __restrict__ obs_rgb, WeightsC wt,
                                                  double* __restrict__ grad, unsigned* __restrict__ marks,
-                                                 int* __restrict__ list, double* __restrict__ partials) {
+                                                 int* __restrict__ list, double* __restrict__ partials,
+                                                 const double* __restrict__ pp, int np,
+                                                 double* __restrict__ last_cost) {
     __shared__ BlockPose sp;
     __shared__ double wsum[4];
+    // the workgroup past the tiles totals the objective before the last step
+    if (last_cost && blockIdx.x == gridDim.x - 1) {
+        gd_cost_block(pp, np, last_cost, wsum);
+        return;
+    }
     extern __shared__ __align__(16) unsigned lbits[];   // the bits, then (every ray marched) the windows
     GdScatter& T = *reinterpret_cast<GdScatter*>(lbits);
     lds_u32* const fb = block_setup(g, gbits, lbits, pose, &sp);   // synchronises the workgroup
@@ -1329,10 +1336,11 @@ hipError_t launch_render_jac(const GridC& g, const CamC& c, const GridD& gd, con
 hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const CamD& cd, const float* map,
                           const unsigned* bits, const prism_pose* pose, const float* obs_depth, const float* obs_rgb,
                           const WeightsC& w, double* grad, unsigned* marks, int* list, double* partials,
-                          hipStream_t st) {
+                          const double* pp, double* last_cost, hipStream_t st) {
     const size_t lds = std::max(bits_lds(g, bits), sizeof(GdScatter));
-    k_gd_grad<<<render_blocks(c), 256, lds, st>>>(g, c, gd, cd, map, bits, pose, obs_depth, obs_rgb, w, grad, marks,
-                                                  list, partials);
+    k_gd_grad<<<render_blocks(c) + (last_cost ? 1 : 0), 256, lds, st>>>(g, c, gd, cd, map, bits, pose, obs_depth,
+                                                                        obs_rgb, w, grad, marks, list, partials, pp,
+                                                                        gd_update_groups(g), last_cost);
     return hipGetLastError();
 }
 

@@ -402,6 +402,45 @@ def test_scatter_boxes(n, width, height, kind):
     assert np.count_nonzero(maps[0].cpu().numpy() != mean) > 20
 
 
+@pytest.mark.parametrize("steps", [2, 3])
+def test_descent_run_is_its_steps(steps):
+    """A descent run against as many runs of one step, where bricks proven free
+    turn occupied between the steps (the surface is pulled towards the camera):
+    a run's later passes must see them, and each step's objective must be its
+    own.  With prior variances of 1e20 a run's prior term (from its first
+    means) is below rounding, so both do the same sums: objectives within 1e-6
+    (the order of the sums can move a stored mean by an ulp), means within
+    1e-6 of max(|mean|, 1e-2) but for a thousandth of those moved (a crossing
+    that such an ulp decides)."""
+    banner(f"descent run of {steps} steps")
+    n = 128
+    c = synth.trajectory_case(seed=3, n=n, width=320, height=240, n_samples=64, n_frames=1)
+    mean = np.asarray(synth.gt_map(c["scene"])[0], np.float32)
+    g, cam = grid_of(c["scene"]), cam_of(c["cam"])
+    pt = P().poses_tensor(synth.pose7(c["traj"].t[0], c["traj"].q[0]))
+    run, ones = (gpu_map(g, mean, np.full_like(mean, 1e20)) for _ in range(2))
+    r = P().render(g, run, cam, pt)
+    D, C, w = r["depth"][0] - 0.05, r["rgb"][0], P().Weights.make()
+    ws = P().map_gd_workspace(g, cam)
+    cost, each = (torch.zeros(steps, dtype=torch.float64, device=DEV) for _ in range(2))
+    P().map_gd(g, run, cam, pt, D, C, w, 3e-3, 3e-3, steps, ws, cost)
+    free = lambda m: m[0].reshape(n // 8, 8, n // 8, 8, n // 8, 8).max((1, 3, 5)) <= 0
+    for k in range(steps):
+        P().map_gd(g, ones, cam, pt, D, C, w, 3e-3, 3e-3, 1, ws, each[k:k + 1])
+        if k == 0:
+            assert (free(mean) & ~free(ones.to_dense()[0].cpu().numpy())).sum() >= 5
+    np.testing.assert_allclose(cost.cpu().numpy(), each.cpu().numpy(), rtol=1e-6)
+    a, b = (m.to_dense()[0].cpu().numpy().astype(np.float64) for m in (run, ones))
+    bad = np.abs(a - b) > 1e-6 * np.maximum(np.abs(b), 1e-2)
+    assert bad.sum() <= 1e-3 * np.count_nonzero(b != mean)
+    # the run leaves the summary and both bitmaps as a recomputation would
+    again = P().VoxelMap(g)
+    again.buf.copy_(run.buf)
+    again.refresh()
+    assert torch.equal(again.buf, run.buf)
+
+
+
 def test_map_gd_full_size(big):
     """Descent mapping at the size of the closed-form comparison: 256^3 FP32,
     320x240, K = 128, one step from a perturbed previous belief (means of
