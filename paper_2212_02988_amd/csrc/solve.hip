@@ -874,78 +874,97 @@ __global__ __launch_bounds__(64) void k_first_frame_batch(BatchArgs b) { first_f
 // n_b.  If P is not positive definite every sample starts at the mean and
 // *flags gets PRISM_FLAG_CHOL_FALLBACK (else 0; written by the first
 // workgroup).
-__global__ __launch_bounds__(64) void k_rollout_sample(const prism_filter_state* __restrict__ S,
-                                                       const prism_filter_bias_state* __restrict__ X,
-                                                       const double* __restrict__ u, int k,
-                                                       const double* __restrict__ noise, TransC tc,
-                                                       prism_pose* __restrict__ poses, int32_t* __restrict__ flags) {
-    __shared__ double A[225];
-    __shared__ int ok;
+//
+// A sample is one chain of small dependent steps, run by one wavefront (its
+// lanes hold the same values) at the latency of the arithmetic: the controls
+// and the noise of kRolloutChunk steps are fetched at once.
+constexpr int kRolloutChunk = 16;
+
+__device__ __forceinline__ void rollout_sample_block(int sample, const prism_filter_state* __restrict__ S,
+                                                     const prism_filter_bias_state* __restrict__ X,
+                                                     const double* __restrict__ u, int k,
+                                                     const double* __restrict__ noise, const TransC& tc,
+                                                     prism_pose* __restrict__ poses, int32_t* __restrict__ flags) {
+    __shared__ double A[225], sz[kRolloutChunk * 15], su[kRolloutChunk * 6];
+    const int lane = threadIdx.x;
+    if (lane >= 64) return;
     const int N = X ? 15 : 12;
-    for (int e = threadIdx.x; e < N * N; e += blockDim.x) A[e] = X ? X->P[e] : S->P[e];
-    __syncthreads();
-    if (threadIdx.x == 0) ok = X ? chol<15>(A) : chol<12>(A);
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    if (blockIdx.x == 0 && flags) *flags = ok ? 0 : PRISM_FLAG_CHOL_FALLBACK;
-    const double* z = noise + (long long)blockIdx.x * (k + 1) * N;
+    const double* z = noise + (long long)sample * (k + 1) * N;
+    for (int e = lane; e < N * N; e += 64) A[e] = X ? X->P[e] : S->P[e];
+    if (lane < N) sz[lane] = z[lane];
+    prism_pose x = S->pose;
+    double v[3], w[3], b[3], sq[15];
+    for (int i = 0; i < 3; ++i) {
+        v[i] = S->v[i];
+        w[i] = S->w[i];
+        b[i] = X ? X->b[i] : 0.0;
+    }
+    for (int i = 0; i < N; ++i) sq[i] = sqrt(tc.q[i]);
+    wave_lds_order();
+    bool ok = false;
+    if (lane == 0) ok = X ? chol<15>(A) : chol<12>(A);
+    ok = __builtin_amdgcn_readfirstlane((int)ok);
+    wave_lds_order();
+    if (lane == 0 && sample == 0 && flags) *flags = ok ? 0 : PRISM_FLAG_CHOL_FALLBACK;
     double e[15];
     for (int i = 0; i < N; ++i) {
         double acc = 0.0;
         if (ok)
-            for (int j = 0; j <= i; ++j) acc += A[i * N + j] * z[j];
+            for (int j = 0; j <= i; ++j) acc += A[i * N + j] * sz[j];
         e[i] = acc;
     }
-    prism_pose x = S->pose;
     retract(x, e);
-    double v[3], w[3], b[3], sq[15];
     for (int i = 0; i < 3; ++i) {
-        v[i] = S->v[i] + e[6 + i];
-        w[i] = S->w[i] + e[9 + i];
-        b[i] = X ? X->b[i] + e[12 + i] : 0.0;
+        v[i] += e[6 + i];
+        w[i] += e[9 + i];
+        if (X) b[i] += e[12 + i];
     }
-    for (int i = 0; i < N; ++i) sq[i] = sqrt(tc.q[i]);
-    for (int j = 0; j < k; ++j) {
-        const double* zj = z + (j + 1) * N;
-        const double* uj = u + 6 * j;
-        double n[15];
-        for (int i = 0; i < N; ++i) n[i] = sq[i] * zj[i];
-        if (X) {
-            double R[9];
+    for (int j0 = 0; j0 < k; j0 += kRolloutChunk) {
+        const int steps = min(k - j0, kRolloutChunk);
+        wave_lds_order();
+        for (int i = lane; i < steps * N; i += 64) sz[i] = z[(long long)(j0 + 1) * N + i];
+        for (int i = lane; i < steps * 6; i += 64) su[i] = u[6 * (long long)j0 + i];
+        wave_lds_order();
+        for (int j = 0; j < steps; ++j) {
+            const double* zj = sz + j * N;
+            const double* uj = su + 6 * j;
+            double n[15], R[9];
+            for (int i = 0; i < N; ++i) n[i] = sq[i] * zj[i];
             quat_to_R9(x.q, R);
-            const double f[3] = {uj[0] - b[0], uj[1] - b[1], uj[2] - b[2]};
-            for (int i = 0; i < 3; ++i) {
-                const double a = R[i * 3] * f[0] + R[i * 3 + 1] * f[1] + R[i * 3 + 2] * f[2] + tc.g[i];
-                v[i] = v[i] + a * tc.du + n[6 + i];
-                w[i] = w[i] + uj[3 + i] * tc.du + n[9 + i];
+            if (X) {
+                const double f[3] = {uj[0] - b[0], uj[1] - b[1], uj[2] - b[2]};
+                for (int i = 0; i < 3; ++i) {
+                    const double a = R[i * 3] * f[0] + R[i * 3 + 1] * f[1] + R[i * 3 + 2] * f[2] + tc.g[i];
+                    v[i] = v[i] + a * tc.du + n[6 + i];
+                    w[i] = w[i] + uj[3 + i] * tc.du + n[9 + i];
+                }
+                for (int i = 0; i < 3; ++i) b[i] += n[12 + i];
+            } else {
+                for (int i = 0; i < 3; ++i) {
+                    v[i] = v[i] + uj[i] * tc.du + n[6 + i];
+                    w[i] = w[i] + uj[3 + i] * tc.du + n[9 + i];
+                }
             }
-            for (int i = 0; i < 3; ++i) b[i] += n[12 + i];
-        } else {
-            for (int i = 0; i < 3; ++i) {
-                v[i] = v[i] + uj[i] * tc.du + n[6 + i];
-                w[i] = w[i] + uj[3 + i] * tc.du + n[9 + i];
-            }
+            const double phi[3] = {w[0] * tc.dt, w[1] * tc.dt, w[2] * tc.dt};
+            double E1[9], E2[9], T[9], R2[9];
+            so3_exp_step(n + 3, E1);
+            so3_exp_step(phi, E2);
+            mat3mul(E2, R, T);
+            mat3mul(E1, T, R2);
+            for (int i = 0; i < 3; ++i) x.t[i] = x.t[i] + v[i] * tc.dt + n[i];
+            R9_to_quat(R2, x.q);
+            if (lane == 0) poses[(long long)sample * k + j0 + j] = x;
         }
-        double phi[3] = {w[0] * tc.dt, w[1] * tc.dt, w[2] * tc.dt};
-        double E1[9], E2[9], R[9], T[9], R2[9];
-        so3_exp(n + 3, E1, nullptr);
-        so3_exp(phi, E2, nullptr);
-        quat_to_R9(x.q, R);
-        mat3mul(E2, R, T);
-        mat3mul(E1, T, R2);
-        for (int i = 0; i < 3; ++i) x.t[i] = x.t[i] + v[i] * tc.dt + n[i];
-        R9_to_quat(R2, x.q);
-        poses[(long long)blockIdx.x * k + j] = x;
     }
 }
 
 // Closed-form (linearised) prediction of the belief over the k controls:
 // mean[j] = (t, q, v, w) after control j (13 doubles), cov[j] = its 12x12
 // covariance; the same propagation as the filter's prediction step.
-__global__ __launch_bounds__(256) void k_rollout_moments(const prism_filter_state* __restrict__ S,
-                                                         const double* __restrict__ u, int k, TransC tc,
-                                                         double* __restrict__ mean, double* __restrict__ cov) {
-    __shared__ double T1[144], T2[144], P[144];
+__device__ __forceinline__ void rollout_moments_block(const prism_filter_state* __restrict__ S,
+                                                      const double* __restrict__ u, int k, const TransC& tc,
+                                                      double* __restrict__ mean, double* __restrict__ cov) {
+    __shared__ double T1[144], T2[144], P[144], su[kRolloutChunk * 6];
     __shared__ double vnew[6], E[9], Jl[9], v[3], w[3];
     __shared__ prism_pose pose;
     if (threadIdx.x == 0) {
@@ -956,11 +975,15 @@ __global__ __launch_bounds__(256) void k_rollout_moments(const prism_filter_stat
         }
     }
     for (int e = threadIdx.x; e < 144; e += blockDim.x) P[e] = S->P[e];
-    __syncthreads();
     for (int j = 0; j < k; ++j) {
+        if (j % kRolloutChunk == 0) {
+            // (thread 0 has left the chunk before: a step ends with a barrier)
+            if ((int)threadIdx.x < 6 * min(k - j, kRolloutChunk)) su[threadIdx.x] = u[6 * (long long)j + threadIdx.x];
+            __syncthreads();
+        }
         if (threadIdx.x == 0) {
             prism_pose pr;
-            transition_mean_t0(pose, v, w, u + 6 * j, tc, vnew, E, Jl, pr);
+            transition_mean_t0(pose, v, w, su + 6 * (j % kRolloutChunk), tc, vnew, E, Jl, pr);
             pose = pr;
             for (int i = 0; i < 3; ++i) {
                 v[i] = vnew[i];
@@ -985,12 +1008,12 @@ __global__ __launch_bounds__(256) void k_rollout_moments(const prism_filter_stat
 
 // The same for the 15-D state: mean[j] = (t, q, v, w, b) (16 doubles),
 // cov[j] its 15x15 covariance.
-__global__ __launch_bounds__(256) void k_rollout_moments_bias(const prism_filter_state* __restrict__ S,
-                                                              const prism_filter_bias_state* __restrict__ X,
-                                                              const double* __restrict__ u, int k, TransC tc,
-                                                              double* __restrict__ mean, double* __restrict__ cov) {
+__device__ __forceinline__ void rollout_moments_bias_block(const prism_filter_state* __restrict__ S,
+                                                           const prism_filter_bias_state* __restrict__ X,
+                                                           const double* __restrict__ u, int k, const TransC& tc,
+                                                           double* __restrict__ mean, double* __restrict__ cov) {
     constexpr int N = 15;
-    __shared__ double M[N * N], G[N * N], T1[N * N], T2[N * N], P[N * N];
+    __shared__ double M[N * N], G[N * N], T1[N * N], T2[N * N], P[N * N], su[kRolloutChunk * 6];
     __shared__ double vnew[6], E[9], Jl[9], Ra[3], R0[9], v[3], w[3], b[3];
     __shared__ prism_pose pose;
     if (threadIdx.x == 0) {
@@ -1002,11 +1025,14 @@ __global__ __launch_bounds__(256) void k_rollout_moments_bias(const prism_filter
         }
     }
     for (int e = threadIdx.x; e < N * N; e += blockDim.x) P[e] = X->P[e];
-    __syncthreads();
     for (int j = 0; j < k; ++j) {
+        if (j % kRolloutChunk == 0) {
+            if ((int)threadIdx.x < 6 * min(k - j, kRolloutChunk)) su[threadIdx.x] = u[6 * (long long)j + threadIdx.x];
+            __syncthreads();
+        }
         if (threadIdx.x == 0) {
             prism_pose pr;
-            transition_mean_bias_t0(pose, v, w, b, u + 6 * j, tc, vnew, E, Jl, Ra, R0, pr);
+            transition_mean_bias_t0(pose, v, w, b, su + 6 * (j % kRolloutChunk), tc, vnew, E, Jl, Ra, R0, pr);
             pose = pr;
             for (int i = 0; i < 3; ++i) {
                 v[i] = vnew[i];
@@ -1030,22 +1056,31 @@ __global__ __launch_bounds__(256) void k_rollout_moments_bias(const prism_filter
     }
 }
 
+// The moments and the samples know nothing of each other and each is one chain:
+// they run side by side, the moments in the first workgroup (when they are
+// wanted).  16 samples of 10 controls: 29 and 37 us one after the other, 30
+// together.
+__global__ __launch_bounds__(256) void k_rollout(const prism_filter_state* __restrict__ S,
+                                                 const prism_filter_bias_state* __restrict__ X,
+                                                 const double* __restrict__ u, int k, TransC tc, int moments,
+                                                 double* __restrict__ mean, double* __restrict__ cov,
+                                                 const double* __restrict__ noise, prism_pose* __restrict__ poses,
+                                                 int32_t* __restrict__ flags) {
+    if ((int)blockIdx.x >= moments)
+        rollout_sample_block(blockIdx.x - moments, S, X, u, k, noise, tc, poses, flags);
+    else if (X)
+        rollout_moments_bias_block(S, X, u, k, tc, mean, cov);
+    else
+        rollout_moments_block(S, u, k, tc, mean, cov);
+}
+
 hipError_t launch_rollout(const prism_filter_state* S, const prism_filter_bias_state* X, const double* u, int k,
                           int n_samples, const double* noise, const TransC& tc, prism_pose* poses, double* mean,
                           double* cov, int32_t* flags, hipStream_t st) {
-    if (mean || cov) {
-        if (X)
-            k_rollout_moments_bias<<<1, 256, 0, st>>>(S, X, u, k, tc, mean, cov);
-        else
-            k_rollout_moments<<<1, 256, 0, st>>>(S, u, k, tc, mean, cov);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (n_samples > 0) {
-        k_rollout_sample<<<n_samples, 64, 0, st>>>(S, X, u, k, noise, tc, poses, flags);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    const int moments = mean || cov ? 1 : 0;
+    if (moments + n_samples == 0) return hipSuccess;
+    k_rollout<<<moments + n_samples, 256, 0, st>>>(S, X, u, k, tc, moments, mean, cov, noise, poses, flags);
+    return hipGetLastError();
 }
 
 // per-frame fixed-order sum of block partials (NV values each)

@@ -852,3 +852,29 @@ def test_pool_smaller_than_grid_matches_oracle(big, dtype):
         assert v.sum() > 10000
         assert np.all(depth_close(out["depth"][i].cpu().numpy()[v], ref["depth"][v]))
         assert np.all(rgb_close(out["rgb"][i].cpu().numpy()[v], ref["rgb"][v]))
+
+
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 33])
+def test_rollout_lengths(k):
+    """Sampled poses and moments of rollouts around the 16 controls that are
+    fetched at once, against the oracle: at most 33 steps of values up to ~1e2
+    in double precision, so 1e-9 (poses, means) leaves a factor of 100; the
+    covariance as in the four-step test."""
+    banner(f"rollout of {k} controls")
+    c = synth.trajectory_case(seed=2, n=64, width=80, height=60, n_samples=32, n_frames=1)
+    tr = c["traj"]
+    f = P().Filter(grid_of(c["scene"], 0), cam_of(c["cam"]), P().FilterParams(objective=0))
+    rng = np.random.default_rng(11)
+    A = rng.normal(size=(12, 12)) * 0.01
+    Pb = A @ A.T + np.diag([1e-5] * 6 + [1e-4] * 6)
+    x = dict(t=tr.t[0], q=tr.q[0], v=tr.v[0], w=tr.w[0])
+    f.reset(np.concatenate([x["t"], x["q"], x["v"], x["w"]]), Pb)
+    u, z = rng.normal(size=(k, 6)), rng.normal(size=(3, k + 1, 12))
+    out = f.rollout(t(u, torch.float64), t(z, torch.float64), moments=True)
+    ref = orc.rollout(None, None, None, x, Pb, u, z, orc.Params(), frames=False)
+    pg = out["poses"].cpu().numpy()
+    for s in range(3):
+        for j in range(k):
+            assert np.linalg.norm(orc.pose_error(pg[s, j], ref["poses"][s, j])) < 1e-9
+    np.testing.assert_allclose(out["mean"].cpu().numpy(), ref["mean"], rtol=0, atol=1e-9)
+    assert np.linalg.norm(out["cov"].cpu().numpy() - ref["cov"]) <= 1e-10 * np.linalg.norm(ref["cov"])
