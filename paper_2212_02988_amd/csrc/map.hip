@@ -80,34 +80,49 @@ __global__ __launch_bounds__(256) void k_pool_init(int nbricks, float pocc, floa
 // flight before the first store.  (One voxel per lane in brick order made a
 // wavefront touch eight 32-byte pieces of eight lines, whose other pieces
 // belong to workgroups of other XCDs, each fetching the line again.)  Measured
-// on a 384^3 BF16 map, loaded and exported: 2484 -> 1030 us, 5.3 TB/s of the
-// bytes both need, where a large plain copy reaches 4.7.
+// on a 384^3 BF16 map, loaded and exported: 2484 -> 1030 us through the caches,
+// 983 past them (5.5 TB/s of the bytes both need; a large plain copy reaches
+// 4.7).
 typedef float float4v __attribute__((ext_vector_type(4)));
 // four floats of a caller's dense array, which is only 4-byte aligned
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint16_t bf16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float4v ld4(const float* p, long long i) {
-    return *reinterpret_cast<const float4v*>(p + i);
+// (non-temporal: a map loaded whole is read again only after the caches have
+// seen the rest of it)
+__device__ __forceinline__ void st4(float* p, long long i, float4v v) {
+    __builtin_nontemporal_store(v, reinterpret_cast<float4v*>(p + i));
 }
-__device__ __forceinline__ float4v ld4(const uint16_t* p, long long i) {
-    const bf16x4 h = *reinterpret_cast<const bf16x4*>(p + i);
-    float4v v;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = __uint_as_float((uint32_t)h[q] << 16);
-    return v;
-}
-__device__ __forceinline__ void st4(float* p, long long i, float4v v) { *reinterpret_cast<float4v*>(p + i) = v; }
 __device__ __forceinline__ void st4(uint16_t* p, long long i, float4v v) {
     bf16x4 h;
 #pragma unroll
     for (int q = 0; q < 4; ++q) h[q] = f2bf(v[q]);
-    *reinterpret_cast<bf16x4*>(p + i) = h;
+    __builtin_nontemporal_store(h, reinterpret_cast<bf16x4*>(p + i));
 }
 __device__ __forceinline__ float4v ldu4(const float* p, long long i) {
     return *reinterpret_cast<const float4u*>(p + i);
 }
 __device__ __forceinline__ void stu4(float* p, long long i, float4v v) { *reinterpret_cast<float4u*>(p + i) = v; }
+
+// The same past the caches (non-temporal), for passes over far more than they
+// hold: a line that such a pass leaves behind only pushes out others, dirty ones
+// among them.
+__device__ __forceinline__ float4v ld4_stream(const float* p, long long i) {
+    return __builtin_nontemporal_load(reinterpret_cast<const float4v*>(p + i));
+}
+__device__ __forceinline__ float4v ld4_stream(const uint16_t* p, long long i) {
+    const bf16x4 h = __builtin_nontemporal_load(reinterpret_cast<const bf16x4*>(p + i));
+    float4v v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = __uint_as_float((uint32_t)h[q] << 16);
+    return v;
+}
+__device__ __forceinline__ float4v ldu4_stream(const float* p, long long i) {
+    return __builtin_nontemporal_load(reinterpret_cast<const float4u*>(p + i));
+}
+__device__ __forceinline__ void stu4_stream(float* p, long long i, float4v v) {
+    __builtin_nontemporal_store((float4u)v, reinterpret_cast<float4u*>(p + i));
+}
 
 // a lane's four voxels of slice k of the four bricks from (4 xg, by): the
 // brick of the lane, the offset within it, the dense index (in: x < n)
@@ -177,8 +192,8 @@ __global__ __launch_bounds__(256) void k_from_dense(int n, int nb, T* __restrict
         for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                if (mean4) v[s][c] = ldu4(mean4, c * nvox + a0.dense + s * d4);
-                if (var4) w[s][c] = ldu4(var4, c * nvox + a0.dense + s * d4);
+                if (mean4) v[s][c] = ldu4_stream(mean4, c * nvox + a0.dense + s * d4);
+                if (var4) w[s][c] = ldu4_stream(var4, c * nvox + a0.dense + s * d4);
             }
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -228,13 +243,13 @@ __global__ __launch_bounds__(256) void k_to_dense(GridC g, const T* __restrict__
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const float prior = c == 0 ? g.pocc : g.prgb;
-        if (mean4) m[c] = !Pool || slot >= 0 ? ld4(map, c * g.nvox + e) : float4v(prior);
-        if (var4) w[c] = !Pool || slot >= 0 ? ld4(map, (4 + c) * g.nvox + e) : float4v(v0);
+        if (mean4) m[c] = !Pool || slot >= 0 ? ld4_stream(map, c * g.nvox + e) : float4v(prior);
+        if (var4) w[c] = !Pool || slot >= 0 ? ld4_stream(map, (4 + c) * g.nvox + e) : float4v(v0);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        if (mean4) stu4(mean4, c * nvox + a.dense, m[c]);
-        if (var4) stu4(var4, c * nvox + a.dense, w[c]);
+        if (mean4) stu4_stream(mean4, c * nvox + a.dense, m[c]);
+        if (var4) stu4_stream(var4, c * nvox + a.dense, w[c]);
     }
 }
 
@@ -261,7 +276,9 @@ __global__ __launch_bounds__(256) void k_planes(int n, int nb, int channels, con
 // the map update).  Bound by the read of the occupancy plane: a workgroup
 // takes the 32 bricks of one word of bits, eight per wavefront, whose loads
 // (16 bytes per lane) are all issued before the first maximum is formed, and
-// the word is packed here rather than by a pass of its own.
+// the word is packed here rather than by a pass of its own.  256^3 FP32: 25 us
+// with cached loads (2.7 TB/s), 13.5 past the caches; the render that follows
+// finds fewer of its lines there and takes 65 instead of 60.
 template <typename T, bool Pool>
 __global__ __launch_bounds__(256) void k_brick_summary(GridC g, const T* __restrict__ map, MapAux aux, int nbricks) {
     __shared__ unsigned wbits[4];
@@ -280,8 +297,8 @@ __global__ __launch_bounds__(256) void k_brick_summary(GridC g, const T* __restr
         }
         const T* p = map + (slot << 9);
         // halves of the brick (FP32 1 KB, BF16 512 bytes each)
-        v[j][0] = ld4(p, 4 * lane);
-        v[j][1] = ld4(p, 256 + 4 * lane);
+        v[j][0] = ld4_stream(p, 4 * lane);
+        v[j][1] = ld4_stream(p, 256 + 4 * lane);
     }
     unsigned mine = 0;
 #pragma unroll
