@@ -155,8 +155,8 @@ __device__ __forceinline__ int sym6(int i, int j) {
     return a * 6 - a * (a - 1) / 2 + b - a;
 }
 
-// Fixed-order block sum of partial sums (nblocks rows of NV doubles, 29 for
-// the normal equations) into lds_out[NV], by the first kSumThreads threads of
+// Fixed-order block sum of partial sums (nblocks rows of NV = 29 doubles, the
+// normal equations) into lds_out[NV], by the first kSumThreads threads of
 // the workgroup (the others only meet the barriers).  The rows are read as one
 // flat array with coalesced loads: thread t < NV G (G = row groups) reads
 // elements t, t + NV G, ... which all belong to column t mod NV; the G sums of
@@ -171,13 +171,12 @@ __device__ __forceinline__ int sym6(int i, int j) {
 // them) and stored to LDS before the sum's barrier.
 constexpr int kSumThreads = 512;
 
-template <int NV = PRISM_NEQ>
 __device__ inline void sum_partials(const double* __restrict__ partials, int nblocks, double* lds_red,
                                     double* lds_out, const prism_filter_state* __restrict__ sg = nullptr,
                                     prism_filter_state* ls = nullptr) {
     constexpr int kStateWords = (int)(sizeof(prism_filter_state) / 8);
     static_assert(sizeof(prism_filter_state) % 8 == 0 && kStateWords <= kSumThreads, "a state word per thread");
-    constexpr int G = kSumThreads / NV, span = G * NV, kRound = 20;
+    constexpr int NV = PRISM_NEQ, G = kSumThreads / NV, span = G * NV, kRound = 20;
     const int t = threadIdx.x;
     unsigned long long sw = 0;
     if (sg && t < kStateWords) sw = reinterpret_cast<const unsigned long long*>(sg)[t];
@@ -1083,13 +1082,46 @@ hipError_t launch_rollout(const prism_filter_state* S, const prism_filter_bias_s
     return hipGetLastError();
 }
 
-// per-frame fixed-order sum of block partials (NV values each)
+// Per-frame fixed-order sum of block partials (NV values each), eight columns
+// per workgroup: one CU reads a frame's rows at its own rate (1200 rows of 29:
+// 6.3 us by one workgroup, 4.7 by four), and 64 threads per column have a frame
+// of 1280 rows in flight at once.
 template <int NV>
-__global__ __launch_bounds__(kSumThreads) void k_finalize(const double* __restrict__ partials, int nblocks,
+__global__ __launch_bounds__(512) void k_finalize(const double* __restrict__ partials, int nblocks,
                                                   double* __restrict__ out) {
-    __shared__ double red[kSumThreads], sums[NV];
-    sum_partials<NV>(partials + (long long)blockIdx.x * nblocks * NV, nblocks, red, sums);
-    if ((int)threadIdx.x < NV) out[(long long)blockIdx.x * NV + threadIdx.x] = sums[threadIdx.x];
+    __shared__ double red[8][8];
+    constexpr int kRound = 20;
+    const int col = (int)blockIdx.y * 8 + (threadIdx.x & 7);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    if (col < NV) {
+        const double* p = partials + (long long)blockIdx.x * nblocks * NV + col;
+        for (int r0 = threadIdx.x >> 3; r0 < nblocks; r0 += 64 * kRound) {
+            double x[kRound];
+#pragma unroll
+            for (int k = 0; k < kRound; ++k) x[k] = r0 + 64 * k < nblocks ? p[(long long)(r0 + 64 * k) * NV] : 0.0;
+#pragma unroll
+            for (int k = 0; k < kRound; ++k) a[k & 3] += x[k];
+        }
+    }
+    double s = (a[0] + a[1]) + (a[2] + a[3]);
+    // lanes that agree in their low three bits
+    s = add_dpp<0x128>(s);   // row rotate by 8
+    const unsigned lo = (unsigned)__double2loint(s), hi = (unsigned)__double2hiint(s);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    s = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    const unsigned lo2 = (unsigned)__double2loint(s), hi2 = (unsigned)__double2hiint(s);
+    const auto l2 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+    const auto h2 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+    s = __hiloint2double((int)h2[0], (int)l2[0]) + __hiloint2double((int)h2[1], (int)l2[1]);
+    if ((threadIdx.x & 63) < 8) red[threadIdx.x >> 6][threadIdx.x & 7] = s;
+    __syncthreads();
+    if (threadIdx.x < 8 && col < NV) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) t += red[w][threadIdx.x];
+        out[(long long)blockIdx.x * NV + col] = t;
+    }
 }
 
 hipError_t launch_predict(prism_filter_state* S, prism_filter_bias_state* X, const double* u, const TransC& tc,
@@ -1141,12 +1173,12 @@ hipError_t launch_first_frame_batch(const BatchArgs& b, hipStream_t st) {
 }
 
 hipError_t launch_finalize(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
-    k_finalize<PRISM_NEQ><<<n_frames, kSumThreads, 0, st>>>(partials, nblocks, out);
+    k_finalize<PRISM_NEQ><<<dim3(n_frames, (PRISM_NEQ + 7) / 8), 512, 0, st>>>(partials, nblocks, out);
     return hipGetLastError();
 }
 
 hipError_t launch_finalize6(const double* partials, int nblocks, int n_frames, double* out, hipStream_t st) {
-    k_finalize<6><<<n_frames, kSumThreads, 0, st>>>(partials, nblocks, out);
+    k_finalize<6><<<n_frames, 512, 0, st>>>(partials, nblocks, out);
     return hipGetLastError();
 }
 
