@@ -372,16 +372,10 @@ __device__ __forceinline__ void predict_block(prism_filter_state* __restrict__ S
         prism_pose pr;
         quat_to_R9(S->pose.q, R);
         mat3mul(E, R, R2);
-        Pose64 cur;
-        for (int i = 0; i < 3; ++i) {
-            pr.t[i] = S->pose.t[i] + vnew[i] * tc.dt;
-            cur.t[i] = pr.t[i];
-            for (int k = 0; k < 3; ++k) cur.R[i][k] = R2[i * 3 + k];
-        }
-        const Pose64 anchor = load_pose64(&S->anchor);
+        for (int i = 0; i < 3; ++i) pr.t[i] = S->pose.t[i] + vnew[i] * tc.dt;
         R9_to_quat(R2, pr.q);
         if (threadIdx.x == 64) {
-            if (rel) rel_of(cur, anchor, *rel);
+            if (rel) rel_of(&pr, &S->anchor, *rel);
             S->prior = pr;
             S->iter = pr;
             S->flags = 0;
@@ -639,18 +633,15 @@ __device__ __forceinline__ void gn_step_block(prism_filter_state* __restrict__ S
     double E[9], R2[9];
     so3_exp_step(b + 3, E);
     mat3mul(E, pre.R, R2);
-    Pose64 cur;
     prism_pose it;
-    for (int i = 0; i < 3; ++i) {
-        it.t[i] = pre.t[i] + b[i];
-        cur.t[i] = it.t[i];
-        for (int k = 0; k < 3; ++k) cur.R[i][k] = R2[i * 3 + k];
-    }
+    for (int i = 0; i < 3; ++i) it.t[i] = pre.t[i] + b[i];
     R9_to_quat(R2, it.q);
     if (threadIdx.x == 0) {
         Sg->iter = it;
         Sg->flags = flags;
-        if (rel) rel_of(cur, pre.anchor, *rel);
+        // from the quaternion as it is stored, not from R2: a tracking call at
+        // the stored pose takes the same decisions
+        if (rel) rel_of(load_pose64(&it), pre.anchor, *rel);
     }
 }
 

@@ -985,3 +985,58 @@ def test_rollout_matches_oracle():
     pg = out["poses"].cpu().numpy()
     for s in range(S):
         assert np.linalg.norm(orc.pose_error(pg[s, 0], ref["poses"][s, 0])) < 1e-9
+
+
+# ---------------------------------------------------------------------------
+# the relative pose of the association recipe
+# ---------------------------------------------------------------------------
+def _flat_anchor(f, depth, rgb):
+    """Replace the filter's anchor frame: the given images, everywhere valid,
+    normals along the optical axis."""
+    a = f.anchor()
+    a["depth"].copy_(depth)
+    a["rgb"].copy_(rgb)
+    a["mask"].fill_(1)
+    a["nmask"].fill_(1)
+    a["normals"].copy_(torch.tensor([0.0, 0.0, -1.0], device=DEV).expand_as(a["normals"]))
+    return a
+
+
+@pytest.mark.parametrize("n_gn", [0, 1, 3])
+@pytest.mark.parametrize("bias", [False, True])
+def test_filter_tracks_from_its_stored_pose(n_gn, bias):
+    """A filter's tracking objective is that of track_p2 at the pose it stores:
+    the relative pose is formed from the stored quaternions.  A camera at rest
+    that sees its anchor frame again: every residual is the rounding of the
+    two poses' double-precision algebra, so a pose that differs from the
+    stored one in its last bits gives other sums.  16x16 pixels are one row of
+    sums, which both calls pass on unchanged: equal bit for bit."""
+    banner(f"stored pose n_gn={n_gn} bias={bias}")
+    n, W, H = 16, 16, 16
+    grid = P().Grid.make(n, 0.2, (-1.6, -1.6, -1.6))
+    cam = P().Camera.make(W, H, 12.0, 12.0, 8.0, 8.0, 0.1, 3.0, 16)
+    rng = np.random.default_rng(5)
+    D = t(rng.uniform(1.0, 2.0, (H, W)))
+    C = t(rng.uniform(0.1, 0.9, (H, W, 3)))
+    prm = P().FilterParams(n_gn=n_gn, modes=P().MODE_ACCEL_BIAS if bias else 0, gravity=(0.0, 0.0, 0.0))
+    zero = torch.zeros(6, dtype=torch.float64, device=DEV)
+    moved = 0
+    for _ in range(6):
+        q = rng.normal(size=4)
+        q /= np.linalg.norm(q) * np.sign(q[0])
+        f = P().Filter(grid, cam, prm)
+        f.map.init()
+        x0 = np.concatenate([rng.uniform(-0.3, 0.3, 3), q, np.zeros(9 if bias else 6)])
+        f.reset(x0, np.diag([1e-4] * (15 if bias else 12)))
+        f.step(D, C, None)
+        anchor = _flat_anchor(f, D, C)
+        prev = f.state().anchor
+        f.pose_update(D, C, zero)
+        s = f.state()
+        pose, before = (np.array(list(p.t) + list(p.q)) for p in (s.iter, prev))
+        out = P().track_p2(cam, P().poses_tensor(pose), P().poses_tensor(before), D, C, anchor, f.cfg.w)
+        a, b = np.array(s.neq), out["neq"][0].cpu().numpy()
+        assert a[28] >= 200
+        moved += int(np.any(a[21:27] != 0.0))
+        np.testing.assert_array_equal(a, b)
+    assert moved >= 5     # rounding residuals, not exact zeros
