@@ -529,11 +529,10 @@ __global__ __launch_bounds__(kAdamThreads) void k_pose_adam(
                                                 (red[buf][2][m6] + red[buf][3][m6])) + lpe[buf][m6];
             v2 = ad.beta2 * v2 + (1.0 - ad.beta2) * gi * gi;
             const double di = -lr * gi / (sqrt(v2 * corr) + ad.eps);
-            double d[6], E[9], R2[3][3], dd[3];
+            double d[6], E[9], R2[3][3];
 #pragma unroll
             for (int m = 0; m < 6; ++m) d[m] = lane_value(di, m);
             so3_exp_step(d + 3, E);
-            const Pose64& Q = rel.prev;
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
@@ -542,19 +541,13 @@ __global__ __launch_bounds__(kAdamThreads) void k_pose_adam(
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
                 rel.cur.t[i] += d[i];
-                dd[i] = rel.cur.t[i] - Q.t[i];
 #pragma unroll
                 for (int k = 0; k < 3; ++k) rel.cur.R[i][k] = R2[i][k];
             }
-            if (wv < 4)   // the prior needs the iterate only
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-#pragma unroll
-                    for (int b = 0; b < 3; ++b)
-                        rel.R[a][b] = (float)(Q.R[0][a] * R2[0][b] + Q.R[1][a] * R2[1][b] + Q.R[2][a] * R2[2][b]);
-                    rel.t[a] = (float)(Q.R[0][a] * dd[0] + Q.R[1][a] * dd[1] + Q.R[2][a] * dd[2]);
-                }
         }
+        // outside the contracted block: the samples' pixels are decided with
+        // it (the prior needs the iterate only)
+        if (wv < 4) rel_of(rel.cur, rel.prev, rel);
     };
     for (int step = 0; step < ad.n_steps; step += 2) {
         do_step(step, 0, sa, sb, ib, ia);

@@ -7,6 +7,7 @@ single-precision recipe as the kernels.  Values are compared with the
 tolerances in gpu_util.
 """
 import ctypes
+from fractions import Fraction
 
 import numpy as np
 import pytest
@@ -990,6 +991,13 @@ def test_rollout_matches_oracle():
 # ---------------------------------------------------------------------------
 # the relative pose of the association recipe
 # ---------------------------------------------------------------------------
+def _write_state(f, field, values):
+    """Overwrite a field of doubles of the filter's device state."""
+    a = f._state_off + getattr(P().FilterState, field).offset
+    v = torch.as_tensor(np.asarray(values, np.float64), device=DEV)
+    f.state_buf[a:a + 8 * v.numel()].view(torch.float64).copy_(v)
+
+
 def _flat_anchor(f, depth, rgb):
     """Replace the filter's anchor frame: the given images, everywhere valid,
     normals along the optical axis."""
@@ -1040,3 +1048,92 @@ def test_filter_tracks_from_its_stored_pose(n_gn, bias):
         moved += int(np.any(a[21:27] != 0.0))
         np.testing.assert_array_equal(a, b)
     assert moved >= 5     # rounding residuals, not exact zeros
+
+
+def _fma64(a, b, c):
+    """Round-to-nearest of the exact a b + c."""
+    return float(Fraction(a) * Fraction(b) + Fraction(c))
+
+
+def _edge_cases(count):
+    """Poses and cameras for which the relative translation rounds to another
+    float when its sum of products is contracted, and the anchor pixel of the
+    image centre is inside the image with one of the two floats only.  The
+    current rotation is the identity; yields (anchor quaternion, camera
+    translation, fx, fy, inside) with `inside` by the uncontracted recipe."""
+    f32, rng, u0 = np.float32, np.random.default_rng(11), 8
+    D, out, want = f32(1.0), [], [count // 2, count - count // 2]
+    while sum(want):
+        # anchor: a small rotation, so that row 0 of its transpose is near x
+        q = np.concatenate([[1.0], rng.normal(scale=0.05, size=3)])
+        q /= np.linalg.norm(q)
+        w, x, y, z = (float(v) for v in q)
+        nrm = float(np.sqrt(w * w + x * x + y * y + z * z))
+        w, x, y, z = w / nrm, x / nrm, y / nrm, z / nrm
+        Q = [[1.0 - 2.0 * (y * y + z * z), 2.0 * (x * y - w * z), 2.0 * (x * z + w * y)],
+             [2.0 * (x * y + w * z), 1.0 - 2.0 * (x * x + z * z), 2.0 * (y * z - w * x)],
+             [2.0 * (x * z - w * y), 2.0 * (y * z + w * x), 1.0 - 2.0 * (x * x + y * y)]]
+        # a translation whose x in the anchor frame lies next to the middle of two floats
+        d = [float(v) for v in rng.uniform(-0.1, 0.1, 3)]
+        lo = f32(rng.uniform(-0.9, -0.6))
+        mid = 0.5 * (float(lo) + float(np.nextafter(lo, f32(0.0))))
+        d[0] = (mid - Q[1][0] * d[1] - Q[2][0] * d[2]) / Q[0][0]
+        d[0] += float(np.spacing(d[0])) * int(rng.integers(-2, 3))
+
+        def rel_t(a):
+            p = [Q[k][a] * d[k] for k in range(3)]
+            return f32((p[0] + p[1]) + p[2])
+        fused = {f32(_fma64(Q[2][0], d[2], _fma64(Q[1][0], d[1], Q[0][0] * d[0]))),
+                 f32(_fma64(Q[2][0], d[2], _fma64(Q[0][0], d[0], Q[1][0] * d[1])))}
+        t0 = rel_t(0)
+        if len(fused) > 1 or t0 in fused:
+            continue
+        # the centre pixel's point is (0, 0, D): its column in the anchor frame
+        R = [f32(Q[2][a]) for a in range(3)]      # third column of Q^T I
+        Y2 = f32(f32(R[2] * D) + rel_t(2))
+        quot = [f32(f32(f32(R[0] * D) + tx) / Y2) for tx in (t0, fused.pop())]
+        if quot[0] == quot[1] or Y2 <= 0.5:
+            continue
+        cx = f32(u0 + 0.5)
+        fx = f32(float(cx) / -float(quot[0]))
+        for _ in range(-8, 9):
+            col = [f32(f32(fx * qq) + cx) for qq in quot]
+            if (col[0] >= 0) != (col[1] >= 0):
+                break
+            fx = np.nextafter(fx, f32(0.0)) if col[0] < 0 else np.nextafter(fx, f32(100.0))
+        else:
+            continue
+        inside = int(col[0] >= 0)
+        if want[inside]:
+            want[inside] -= 1
+            out.append((q, d, float(fx), inside))
+    return out
+
+
+def test_adam_decides_without_contraction():
+    """The optimiser's later steps place their samples with the relative pose
+    of the recipe, products and sums rounded one by one.  Poses found so that
+    a fused multiply-add anywhere in that sum moves the anchor pixel of the
+    one sample across the image's border: a sample inside moves the iterate,
+    one outside leaves it as predicted.  (The first of the two steps samples
+    no pixel, so the second starts from the predicted pose.)"""
+    banner("adam at the image border")
+    W = H = 17
+    grid = P().Grid.make(16, 0.2, (-1.6, -1.6, -1.6))
+    D = torch.ones((H, W), device=DEV)
+    C = torch.full((H, W, 3), 0.5, device=DEV)
+    zero = torch.zeros(6, dtype=torch.float64, device=DEV)
+    ap = P().AdamParams.make(n_steps=2, n_pixels=1)
+    pixels = torch.tensor([[-1], [8 * W + 8]], dtype=torch.int32, device=DEV)
+    for q, d, fx, inside in _edge_cases(12):
+        cam = P().Camera.make(W, H, fx, 4.0, 8.5, 8.5, 0.1, 3.0, 16)
+        f = P().Filter(grid, cam, P().FilterParams(gate_geo=1e6))
+        f.map.init()
+        f.reset(np.concatenate([d, [1.0, 0, 0, 0], np.zeros(6)]), np.diag([1e-4] * 12))
+        f.step(D, C, None)
+        _flat_anchor(f, D, C)
+        _write_state(f, "anchor", np.concatenate([np.zeros(3), q]))
+        f.pose_update_adam(D, C, zero, ap, pixels)
+        s = f.state()
+        assert list(s.prior.t) == d and list(s.prior.q)[1:] == [0.0, 0.0, 0.0]
+        assert (list(s.iter.t) != d) == bool(inside), (q, d, fx, inside)
