@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void k_from_dense(int n, int nb, T* __restrict
     const QuadAt a0 = quad_at(n, nb, xg, by, (bz << 3) | wv);
     const long long e0 = (a0.brick << 9) | a0.loc;
     const long long d4 = 4LL * n * n;   // four slices on: 256 elements in the brick
-    float m = -INFINITY;
+    float m = NAN;   // (fmaxf passes over it: a brick without a number keeps it, and is not free)
     if (a0.in) {
         float4v v[2][4], w[2][4];
 #pragma unroll

@@ -72,3 +72,34 @@ def test_plane_copies(n, channels):
         bricks = pr.dense_to_bricks(n, load(dense))
         assert torch.equal(bricks, _bricks(dense, n))
         assert torch.equal(pr.bricks_to_dense(n, load(bricks)), dense)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_summary_of_maps_with_nan(dtype):
+    """The summary of a loaded map is that of the stored means, NaN among
+    them: the largest mean that is a number, and NaN (not free) for a brick
+    that holds none."""
+    banner(f"summary with NaN dtype={dtype}")
+    n, nan = 16, float("nan")
+    mean = torch.full((4, n, n, n), -0.5, device=DEV)
+    mean[0, :8, :8, :8] = nan                                  # brick 0: no number
+    mean[0, :8, :8, 8:] = nan                                  # brick 1: one number, negative
+    mean[0, 3, 4, 13] = -0.25
+    mean[0, :8, 8:, :8] = nan                                  # brick 2: one number, positive
+    mean[0, 7, 15, 0] = 0.25
+    mean[0, 8:, :8, :8] = nan                                  # brick 4: lowest finite value and -infinity
+    mean[0, 8, 0, 0] = -float("inf")
+    mean[0, 9, 1, 1] = torch.finfo(torch.float32).min if dtype == 0 else -3.0e38
+    mean[0, 8:, 8:, 8:] = -float("inf")                        # brick 7
+    grid = P().Grid.make(n, 0.05, dtype=dtype)
+    vm = P().VoxelMap(grid).init()
+    vm.from_dense(mean, None)
+    held = (mean.to(torch.bfloat16).float() if dtype else mean).cpu().numpy()
+    want = np.fmax.reduce(_bricks(torch.from_numpy(held[:1]), n).view(8, 512).numpy(), axis=1)
+    bmax, plain, dil = _aux(grid, vm)
+    np.testing.assert_array_equal(bmax, want)
+    bits = np.unpackbits(np.ascontiguousarray(plain).view(np.uint8), bitorder="little")
+    assert np.array_equal(bits[:8], want <= 0) and np.isnan(want[0]) and not bits[0]
+    vm.refresh()
+    assert all(np.array_equal(a, b, equal_nan=a.dtype == np.float32)
+               for a, b in zip(_aux(grid, vm), (bmax, plain, dil)))
