@@ -439,6 +439,40 @@ def test_descent_run_is_its_steps(steps):
     again.refresh()
     assert torch.equal(again.buf, run.buf)
 
+@pytest.mark.parametrize("n,width,height", [(128, 36, 27), (128, 60, 45), (128, 97, 71), (128, 150, 113)])
+def test_descent_with_pixels_beyond_the_window(n, width, height):
+    """A descent step where a wavefront's pixels reach more voxels than its
+    window holds (pixels from 0.35 to 1.5 voxels wide at 2 m): objective and
+    every mean against the oracle, at the bar of the same comparison at 64^3 /
+    80x60 (there more rays share a voxel, whose weights' rounding sums up),
+    every brick that was added to is visited (accumulators left zero), and the
+    brick summary follows."""
+    banner(f"descent beyond the window n={n} {width}x{height}")
+    c = synth.trajectory_case(seed=3, n=n, width=width, height=height, n_samples=n // 2, n_frames=1)
+    rng = np.random.default_rng(8)
+    mean = np.asarray(synth.gt_map(c["scene"])[0], np.float32)
+    mean = mean + rng.normal(0, 0.01, mean.shape).astype(np.float32)
+    var = rng.uniform(0.5, 2.0, mean.shape).astype(np.float32)
+    g, cam = grid_of(c["scene"]), cam_of(c["cam"])
+    og, oc = orc.grid_from_scene(c["scene"]), orc.cam_from(c["cam"])
+    pose, p = synth.pose7(c["traj"].t[0], c["traj"].q[0]), orc.Params()
+    D, C = c["depth"][0], c["rgb"][0]
+    vm, ws = gpu_map(g, mean, var), P().map_gd_workspace(g, cam)
+    cost = torch.zeros(1, dtype=torch.float64, device=DEV)
+    P().map_gd(g, vm, cam, P().poses_tensor(pose), t(D), t(C),
+               P().Weights.make(p.b_geo, p.b_rgb, p.gate_geo, p.gate_rgb), 3e-6, 3e-3, 1, ws, cost)
+    want, wcost = orc.map_gd(og, mean.astype(np.float64), var.astype(np.float64), oc, pose, D, C, p, 3e-6, 3e-3, 1)
+    np.testing.assert_allclose(cost.cpu().numpy(), wcost, rtol=1e-5)
+    got = vm.to_dense()[0].cpu().numpy().astype(np.float64)
+    err = np.abs(got - want) / np.maximum(np.abs(want), 1e-2)
+    print(f"[descent] {np.count_nonzero(want != mean)} voxels moved, max scaled error {err.max():.2e}", flush=True)
+    assert np.count_nonzero(want != mean) > 3000
+    assert err.max() <= 1e-6
+    assert not ws[:4 * n ** 3 * 8].view(torch.float64).any()
+    again = P().VoxelMap(g)
+    again.buf.copy_(vm.buf)
+    again.refresh()
+    assert torch.equal(again.buf, vm.buf)
 
 
 def test_map_gd_full_size(big):
