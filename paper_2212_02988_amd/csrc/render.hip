@@ -795,10 +795,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // voxel).  Rays that see one surface reach a small box of voxels: the sums
 // live in a window over that box, addressed directly, and go out in window
 // order, where neighbouring lanes hold neighbouring voxels of a brick row and
-// their atomics share cache lines.  (256 voxels hold 99 % of the boxes of a
-// 320x240 view of a 256^3 map of 2.5 cm voxels.)  Rays whose box is larger see
-// surfaces far apart, or voxels that are small beside their pixels, and share
-// few voxels: they add to global memory directly.
+// their atomics share cache lines.  How many boxes a window holds depends on
+// the ratio of pixel to voxel.  Boxes beyond 236 / 256 voxels (double / float
+// windows), first views of two rooms of 6.4 m: 256^3 at 320x240 7-14 / 3-6 %, at
+// 240x180 25-36 / 13-23 %, at 160x120 64-75 / 56-58 %, 384^3 at 320x240
+// 41-49 / 24-37 %.  Beyond it the adjoint adds to global memory directly, which
+// is still faster at all of these than hash tables per tile were (8 frames of
+// 160x120 at 256^3: 167 -> 94 us, 4 at 384^3: 142 -> 113); the descent's dearer
+// atomics first go sample by sample (see k_gd_grad).
 //
 // LDS float atomics would bound a scatter by corners (170 clocks per
 // instruction measured, whether or not lanes meet in an address), so the
@@ -810,15 +814,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k
 // the four lanes of a ray have a plane each, and no other wavefront shares
 // the window.  Measured at 256^3, 320x240 (hash tables per tile before): the
 // adjoint of 8 frames 399 -> 113 us (67 without any scatter), the descent
-// gradient 72 -> 40 us (23; 34 with five workgroups per CU, see Scatter).
+// gradient 72 -> 40 us (23; 34 with five workgroups per CU, see Scatter, and 31
+// with the samples of larger boxes taking turns).
 
 template <typename V, int Copies>
 struct Scatter {
     // voxels per plane; a box of as many spans fewer than 64 bricks.  Double
     // windows are what lets a fifth workgroup onto a CU (32000 bytes each, with
-    // the free-space bits, done with by then, in the same LDS): a 320x240 frame's
-    // 1200 tiles are then all resident at once; the descent gradient takes 37 us
-    // with 256 (four per CU), 34 with 236.
+    // the free-space bits, done with by then, in the same LDS), which pays where
+    // most boxes fit either way, and costs where more of them fit 256.  20 descent
+    // steps with 256 / 236, us: 256^3 at 320x240 946 / 827, 384^3 at 640x480
+    // 2056 / 1929, 128^3 at 320x240 742 / 696; 256^3 at 160x120 826 / 891, 384^3
+    // at 320x240 1416 / 1539; 160x120 and 80x60 otherwise within 2 %.
     static constexpr int kWin = sizeof(V) == 8 ? 236 : 256;
     V win[4][Copies][kWin + 8];   // planes and copies shifted in the banks
 };
@@ -953,29 +960,25 @@ __device__ __forceinline__ void scatter_cell(const GridC& g, Scatter<V, Copies>&
 }
 
 // touched(b) for the bricks that a wavefront without a window added to: those
-// of its rays' in-grid corners (add0, add1: some lane of the ray added to cell
-// c0, c1).  After the atomics, and about once per brick: the rays of a
-// wavefront lie in few bricks, so each looks a brick up in a table (a slot per
-// brick of 8x8x8 neighbours, in LDS the windows leave unused) and only the
-// first reports it.  (Each corner looking at its brick's mark waited for the
-// atomics before it, and in a run's first step many lanes found the mark unset
-// and met in its atomic: the descent gradient of a 320x240 frame of a 384^3
-// map, half of its wavefronts without a window, took 190 us in the first step
-// and 118 in later ones.)
+// of its rays' in-grid corners (add: some lane of the ray added to the cell).
+// After the atomics, and about once per brick: the rays of a wavefront lie in
+// few bricks, so each looks a brick up in a table (a slot per brick of 8x8x8
+// neighbours, in LDS the window leaves unused) and only the first reports it.
+// (Each corner looking at its brick's mark waited for the atomics before it,
+// and in a run's first step many lanes found the mark unset and met in its
+// atomic: 132 -> 190 us for the first step of a 320x240 frame of a 384^3 map.)
 template <typename V, int Copies, typename Touched>
-__device__ __forceinline__ void touch_cells(const GridC& g, Scatter<V, Copies>& S, int s, const Cell& c0, bool add0,
-                                            const Cell& c1, bool add1, const Touched& touched) {
+__device__ __forceinline__ void touch_cells(const GridC& g, Scatter<V, Copies>& S, int s, const Cell& cl, bool add,
+                                            const Touched& touched) {
     constexpr int kSlots = 512;
     static_assert(sizeof(S.win) >= kSlots * sizeof(int), "the table lives in the windows");
     int* const seen = reinterpret_cast<int*>(&S.win);
     for (int e = threadIdx.x & 63; e < kSlots; e += 64) seen[e] = -1;
     wave_lds_order();
-#pragma unroll 1
-    for (int k = 0; k < 4; ++k) {   // the four lanes of a ray take four of its sixteen corners each
-        const Cell& cl = k & 1 ? c1 : c0;
-        const int q = s | ((k & 2) << 1);
-        if (!(k & 1 ? add1 : add0)) continue;
-        const int x = cl.i[0] + (q & 1), y = cl.i[1] + ((q >> 1) & 1), z = cl.i[2] + (q >> 2);
+    if (!add) return;
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz) {   // the four lanes of a ray take two of the eight corners each
+        const int x = cl.i[0] + (s & 1), y = cl.i[1] + (s >> 1), z = cl.i[2] + dz;
         if (max(max((unsigned)x, (unsigned)y), (unsigned)z) >= (unsigned)g.n) continue;
         const int bx = x >> 3, by = y >> 3, bz = z >> 3, b = (bz * g.nb + by) * g.nb + bx;
         if (atomicExch(&seen[((bz & 7) << 6) | ((by & 7) << 3) | (bx & 7)], b) != b) touched(b);
@@ -998,19 +1001,69 @@ __device__ __forceinline__ void window_add(const TileScatter<V, Copies>& T, int 
         for (int k = 0; k < Copies; ++k) sum[p] += T.wave[wv].win[p][k][e];
 }
 
-// The tile's sums to global memory, one atomic per (plane, voxel) that is not
-// zero; touched(b): each brick that received something.  Global atomics bound
-// the scatter once the window sums are cheap, so the four windows are summed
-// on the way out (a voxel on their borders goes out once), over the box of all
-// four in brick order: lanes in eights hold a brick row's voxels.  Windows far
-// apart (a box beyond kTileBox) go out one by one.  The whole workgroup.
+// The sums over a box of voxels to global memory, one atomic per (plane, voxel)
+// that is not zero, in brick order: lanes in eights hold a brick row's voxels.
+// Threads first, first + step, ...; sums(x, y, z, out) gives a voxel's four;
+// touched(b): each brick that received something, through mark (a byte per
+// brick of the box; order() makes them visible among the threads).
+template <typename V, typename Sums, typename Order, typename Touched>
+__device__ __forceinline__ void box_out(const GridC& g, int first, int step, const int lo[3], const int hi[3],
+                                        uint8_t* mark, const Sums& sums, const Order& order, V* __restrict__ grad,
+                                        const Touched& touched) {
+    const int gx0 = lo[0] >> 3, dy = hi[1] - lo[1] + 1, dz = hi[2] - lo[2] + 1;
+    const int ngx = (hi[0] >> 3) - gx0 + 1, vol = ngx * 8 * dy * dz;
+    constexpr bool marks = !std::is_same<Touched, NoMarks>::value;
+    const int by0 = lo[1] >> 3, nby = (hi[1] >> 3) - by0 + 1, bz0 = lo[2] >> 3, nbz = (hi[2] >> 3) - bz0 + 1;
+    if constexpr (marks) {
+        for (int e = first; e < ngx * nby * nbz; e += step) mark[e] = 0;
+        order();
+    }
+    // quotients of small integers by a reciprocal: (r + 1/2) / d is at
+    // least 1/(2d) from an integer
+    const float iy = __builtin_amdgcn_rcpf((float)dy), iz = __builtin_amdgcn_rcpf((float)dz);
+    for (int e = first; e < vol; e += step) {
+        const int r = e >> 3, ry = (int)(((float)r + 0.5f) * iy), gx = (int)(((float)ry + 0.5f) * iz);
+        const int x = ((gx0 + gx) << 3) | (e & 7), y = lo[1] + r - ry * dy, z = lo[2] + ry - gx * dz;
+        V sum[4] = {V(0), V(0), V(0), V(0)};
+        sums(x, y, z, sum);
+        const long long id = vidx(g, x, y, z);
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            if (sum[p] != V(0)) {
+                grad_out(grad + (long long)p * g.nvox + id, sum[p]);
+                if constexpr (marks) mark[(((z >> 3) - bz0) * nby + (y >> 3) - by0) * ngx + gx] = 1;
+            }
+    }
+    // once per box: a look at a brick's mark waits for the atomics before it
+    if constexpr (marks) {
+        order();
+        for (int e = first; e < ngx * nby * nbz; e += step)
+            if (mark[e]) touched(((bz0 + e / (ngx * nby)) * g.nb + by0 + (e / ngx) % nby) * g.nb + gx0 + e % ngx);
+    }
+}
+
+// a wavefront's own window
+template <typename V, int Copies, typename Touched>
+__device__ __forceinline__ void wave_out(const GridC& g, TileScatter<V, Copies>& T, const Window& w,
+                                         V* __restrict__ grad, const Touched& touched) {
+    const int wv = threadIdx.x >> 6;
+    const int lo[3] = {w.x0, w.y0, w.z0}, hi[3] = {w.x0 + w.dx - 1, w.y0 + w.dy - 1, w.z0 + w.dz - 1};
+    box_out(g, (int)(threadIdx.x & 63), 64, lo, hi, T.mark + 64 * wv,
+            [&](int x, int y, int z, V sum[4]) { window_add(T, wv, w, x, y, z, sum); }, [] { wave_lds_order(); }, grad,
+            touched);
+    wave_lds_order();
+}
+
+// The tile's sums to global memory.  Global atomics bound the scatter once the
+// window sums are cheap, so the four windows are summed on the way out (a voxel
+// on their borders goes out once), over the box of all four.  Windows far apart
+// (a box beyond kTileBox) go out one by one.  The whole workgroup.
 constexpr int kTileBox = 2048;   // spans at most 256 bricks
 
 template <typename V, int Copies, typename Touched>
 __device__ __forceinline__ void scatter_flush(const GridC& g, TileScatter<V, Copies>& T, const Window& mine,
                                               V* __restrict__ grad, const Touched& touched) {
-    const int wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) T.at[wv] = mine;
+    if ((threadIdx.x & 63) == 0) T.at[threadIdx.x >> 6] = mine;
     __syncthreads();
     Window w[4];
     int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {-1, -1, -1};
@@ -1026,47 +1079,16 @@ __device__ __forceinline__ void scatter_flush(const GridC& g, TileScatter<V, Cop
         hi[2] = max(hi[2], w[k].z0 + w[k].dz - 1);
     }
     if (hi[0] < 0) return;
-    auto box = [&](int first, int step, const int lo[3], const int hi[3], int k0, int k1, uint8_t* mark, auto&& order) {
-        const int gx0 = lo[0] >> 3, dy = hi[1] - lo[1] + 1, dz = hi[2] - lo[2] + 1;
-        const int ngx = (hi[0] >> 3) - gx0 + 1, vol = ngx * 8 * dy * dz;
-        constexpr bool marks = !std::is_same<Touched, NoMarks>::value;
-        const int by0 = lo[1] >> 3, nby = (hi[1] >> 3) - by0 + 1, bz0 = lo[2] >> 3, nbz = (hi[2] >> 3) - bz0 + 1;
-        if constexpr (marks) {
-            for (int e = first; e < ngx * nby * nbz; e += step) mark[e] = 0;
-            order();
-        }
-        // quotients of small integers by a reciprocal: (r + 1/2) / d is at
-        // least 1/(2d) from an integer
-        const float iy = __builtin_amdgcn_rcpf((float)dy), iz = __builtin_amdgcn_rcpf((float)dz);
-        for (int e = first; e < vol; e += step) {
-            const int r = e >> 3, ry = (int)(((float)r + 0.5f) * iy), gx = (int)(((float)ry + 0.5f) * iz);
-            const int x = ((gx0 + gx) << 3) | (e & 7), y = lo[1] + r - ry * dy, z = lo[2] + ry - gx * dz;
-            V sum[4] = {V(0), V(0), V(0), V(0)};
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k >= k0 && k < k1) window_add(T, k, w[k], x, y, z, sum);
-            const long long id = vidx(g, x, y, z);
-#pragma unroll
-            for (int p = 0; p < 4; ++p)
-                if (sum[p] != V(0)) {
-                    grad_out(grad + (long long)p * g.nvox + id, sum[p]);
-                    if constexpr (marks) mark[(((z >> 3) - bz0) * nby + (y >> 3) - by0) * ngx + gx] = 1;
-                }
-        }
-        // once per box: a look at a brick's mark waits for the atomics before it
-        if constexpr (marks) {
-            order();
-            for (int e = first; e < ngx * nby * nbz; e += step)
-                if (mark[e]) touched(((bz0 + e / (ngx * nby)) * g.nb + by0 + (e / ngx) % nby) * g.nb + gx0 + e % ngx);
-        }
-    };
     const long long vol = ((hi[0] >> 3) - (lo[0] >> 3) + 1) * 8LL * (hi[1] - lo[1] + 1) * (hi[2] - lo[2] + 1);
     if (vol <= kTileBox) {
-        box((int)threadIdx.x, 256, lo, hi, 0, 4, T.mark, [] { __syncthreads(); });
+        box_out(g, (int)threadIdx.x, 256, lo, hi, T.mark,
+                [&](int x, int y, int z, V sum[4]) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) window_add(T, k, w[k], x, y, z, sum);
+                },
+                [] { __syncthreads(); }, grad, touched);
     } else if (mine.vol > 0) {
-        const int l[3] = {mine.x0, mine.y0, mine.z0};
-        const int h[3] = {mine.x0 + mine.dx - 1, mine.y0 + mine.dy - 1, mine.z0 + mine.dz - 1};
-        box((int)(threadIdx.x & 63), 64, l, h, wv, wv + 1, T.mark + 64 * wv, [] { wave_lds_order(); });
+        wave_out(g, T, mine, grad, touched);
     }
 }
 
@@ -1259,9 +1281,32 @@ __global__ __launch_bounds__(256) void k_gd_grad(GridC g, CamC c, GridD gd, CamD
     Scatter<double, 1>& A = T.wave[threadIdx.x >> 6];
     const Window w = scatter_window(g, A, live, c0, c1);
     auto touched = [&](int b) { mark_brick(marks, list, b); };
-    scatter_cell(g, A, w, s, c0, w0, k0, k0 != 0.0, grad);
-    scatter_cell(g, A, w, s, c1, w1, k1, k1 != 0.0, grad);
-    if (w.vol < 0) touch_cells(g, A, s, c0, add0, c1, add1, touched);
+    if (w.vol >= 0) {
+        scatter_cell(g, A, w, s, c0, w0, k0, k0 != 0.0, grad);
+        scatter_cell(g, A, w, s, c1, w1, k1, k1 != 0.0, grad);
+    } else {
+        // The two samples of a ray lie a step apart (over two voxels at K = n / 2),
+        // so the cells of one of them reach half the box of both (a median of 144
+        // voxels, not 288, for 256^3 at 160x120): they take the window in turn,
+        // and it goes out in between.  Beyond the window are then 1 % of the
+        // wavefronts at 256^3 / 320x240 (7-14 % at once), 13-23 % at 160x120
+        // (64-75 %) and 2-5 % at 384^3 / 320x240 (41-49 %).  20 steps at 256^3 /
+        // 320x240 take 826 us instead of 1233, at 384^3 / 320x240 1539 instead of
+        // 2553 (2486 before there were windows); 5 at 256^3 / 160x120 227 / 269.
+#pragma unroll 1
+        for (int k = 0; k < 2; ++k) {
+            const Cell cl = k ? c1 : c0;
+            const float wt[3] = {k ? w1[0] : w0[0], k ? w1[1] : w0[1], k ? w1[2] : w0[2]};
+            const double coef = k ? k1 : k0;
+            const bool add = k ? add1 : add0;
+            const Window own = scatter_window(g, A, add, cl, cl);
+            scatter_cell(g, A, own, s, cl, wt, coef, coef != 0.0, grad);
+            if (own.vol > 0)
+                wave_out(g, T, own, grad, touched);
+            else if (own.vol < 0)
+                touch_cells(g, A, s, cl, add, touched);
+        }
+    }
     scatter_flush(g, T, w, grad, touched);
 }
 
