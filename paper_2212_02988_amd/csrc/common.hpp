@@ -414,14 +414,8 @@ __device__ __forceinline__ void trigrad(const float v[8], const float w[3], floa
 }
 
 // ---------------------------------------------------------------------------
-// reductions of the 29-double normal equations
+// reductions, the 29 sums of the normal equations among them
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
-}
-
 // x + the value of the lane a DPP control selects
 template <int Ctrl>
 __device__ __forceinline__ double add_dpp(double x) {
@@ -466,7 +460,7 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_wave_barrier();
 }
 
-constexpr int kRedLds = 32 * 16;   // doubles of LDS scratch for block_reduce29
+constexpr int kRedLds = 32 * 16;   // doubles of LDS scratch for block_reduce29f
 
 // Descent: the objective before a step, from the step's per-workgroup
 // partials, by a workgroup of 256 threads in a fixed order (part: 4 doubles).
@@ -480,51 +474,19 @@ __device__ inline void gd_cost_block(const double* __restrict__ pp, int np, doub
     if (threadIdx.x == 0) *cost = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
-// Reduce a per-thread 29-vector over the block (blockDim.x a multiple of 64,
-// <= 1024) into out[0..28] (written by threads 0..28).  lds: kRedLds doubles.
+// Reduce per-lane sums of 29 values (a pixel's or ray's few rows) over the block
+// (blockDim.x a multiple of 64, <= 1024) into out[0..28] (written by threads
+// 0..28).  lds: kRedLds doubles.
 //
-// Within a wave the 29 sums use a halving exchange instead of 29 separate
-// butterfly reductions: at the step with offset o (16, 8, 4, 2, 1) each lane
-// keeps the half of its remaining values selected by its lane bit o, sends
-// the other half to lane ^ o and adds what it receives.  After five steps
-// lane l holds value l & 31 summed over its 32-lane half, one more exchange
-// (offset 32) completes the wave sum: 32 double shuffles per wave instead of
-// 29 * 6.  Summation order is fixed, so results are deterministic.
-__device__ inline void block_reduce29(double acc[PRISM_NEQ], double* lds, double* out) {
-    double v[32];
-#pragma unroll
-    for (int q = 0; q < 32; ++q) v[q] = q < PRISM_NEQ ? acc[q] : 0.0;
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int half = 16; half >= 1; half >>= 1) {
-        bool hi = (lane & half) != 0;
-#pragma unroll
-        for (int j = 0; j < half; ++j) {
-            double send = hi ? v[j] : v[j + half];
-            double keep = hi ? v[j + half] : v[j];
-            v[j] = keep + __shfl_xor(send, half, 64);
-        }
-    }
-    double w = v[0] + __shfl_xor(v[0], 32, 64);   // value (lane & 31), whole wave
-    const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    // one row of 32 per wavefront: the stores of a wavefront and the loads of
-    // each step of the sum below hit consecutive doubles (no bank conflicts)
-    if (lane < 32) lds[wv * 32 + lane] = w;
-    __syncthreads();
-    if (threadIdx.x < PRISM_NEQ) {
-        double s = 0.0;
-        for (int k = 0; k < nw; ++k) s += lds[k * 32 + threadIdx.x];
-        out[threadIdx.x] = s;
-    }
-}
-
-// The same for single-precision per-lane sums (a pixel's or ray's few rows):
-// the five halving steps inside each 32-lane half run in single precision
-// (one 4-byte exchange per value instead of two), each lane widens its one
-// remaining value, and the step across halves and the sum over waves are in
-// double precision.  A single-precision sum spans at most 32 lanes (relative
-// error below 32 ulp of the sum of magnitudes); the order is fixed, so
-// results are deterministic.
+// Within 32 lanes the sums use a halving exchange instead of 29 separate
+// butterfly reductions: at the step of width h (16, 8, 4, 2, 1) each lane keeps
+// the half of its remaining values selected by its lane bit h, gives the other
+// half to a partner and adds what it receives, so after five steps lane l holds
+// value l & 31 of its half.  These steps run in single precision, each lane
+// widens its one remaining value, and the step across halves and the sum over
+// waves are in double precision.  A single-precision sum spans at most 32 lanes
+// (relative error below 32 ulp of the sum of magnitudes); the order is fixed,
+// so results are deterministic.
 __device__ inline void block_reduce29f(const float acc[PRISM_NEQ], double* lds, double* out) {
     float v[32];
 #pragma unroll
@@ -592,23 +554,8 @@ __device__ inline void block_reduce29f(const float acc[PRISM_NEQ], double* lds, 
     }
 }
 
-// one residual row (Jacobian row j, residual r, weight w) into the
-// 29-double normal equations, products formed in double precision
-__device__ __forceinline__ void neq_add(double acc[PRISM_NEQ], const float j[6], double r, double w) {
-    double jd[6];
-#pragma unroll
-    for (int a = 0; a < 6; ++a) jd[a] = (double)j[a];
-    int q = 0;
-#pragma unroll
-    for (int a = 0; a < 6; ++a)
-#pragma unroll
-        for (int b = a; b < 6; ++b) acc[q++] += w * jd[a] * jd[b];
-#pragma unroll
-    for (int a = 0; a < 6; ++a) acc[21 + a] += w * jd[a] * r;
-    acc[27] += w * r * r;
-}
-
-// the same in single precision, for one pixel's few rows (fused multiply-
+// one residual row (Jacobian row j, residual r, weight w) into the 29 normal-
+// equation sums in single precision, for one pixel's few rows (fused multiply-
 // adds: these sums are values, no decision depends on their rounding)
 __device__ __forceinline__ void neq_add32(float acc[PRISM_NEQ], const float j[6], float r, float w) {
     float wj[6];
