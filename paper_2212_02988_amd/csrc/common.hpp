@@ -139,7 +139,8 @@ __device__ inline Pose64 load_pose64(const prism_pose* pp) {
 // uses it: R, t (current -> anchor) in single precision for the association
 // recipe, both poses in double precision for the values.  A filter keeps its
 // own copy, formed whenever its iterate changes (predict, Gauss-Newton step)
-// from the poses as they are stored.
+// from the poses as they are stored.  (The Adam optimiser carries its iterate as
+// a rotation matrix during a run and forms R, t from that.)
 struct Rel32 {
     float R[3][3], t[3];   // current camera -> anchor camera (association recipe)
     Pose64 cur, prev;      // both poses in double precision (values)

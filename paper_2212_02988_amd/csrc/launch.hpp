@@ -149,10 +149,12 @@ hipError_t launch_map_update(const GridC& g, const CamC& c, const GridD& gd, int
 int map_update_groups(const GridC& g);
 int map_update_groups_batch(const GridC& g);
 
-// descent mapping (gradient pass, step on marked bricks, cost total)
-// list: [0] number of bricks, then the bricks, in the order first touched;
-// cost (nullable): the objective before the step, from the nd data partials
-// pd and the step's previous-belief partials
+// descent mapping: gradient pass, step on marked bricks, end of a run
+// list: [0] number of bricks, then the bricks, in the order first touched.
+// The gradient pass writes its workgroups' data terms (partials); the step adds
+// them (pd[nd]) to its previous-belief terms in gd_update_groups partials, whose
+// total is the objective before the step.  The next gradient pass forms it from
+// those (pp) in last_cost (nullable), after the last step launch_gd_end in cost.
 hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const CamD& cd, const float* map,
                           const unsigned* bits, const prism_pose* pose, const float* obs_depth, const float* obs_rgb,
                           const WeightsC& w, double* grad, unsigned* marks, int* list, double* partials,
@@ -160,7 +162,7 @@ hipError_t launch_gd_grad(const GridC& g, const CamC& c, const GridD& gd, const 
 hipError_t launch_gd_update(const GridC& g, float* map, const MapAux& aux, float* save, double* grad,
                             const int* list, unsigned* saved, double lr_occ, double lr_rgb, const double* pd, int nd,
                             double* partials, hipStream_t st);
-// after a run's last step: the dilated bits, and cost (if given) from its partials
+// after a run's last step: the dilated bits, and cost (if given) from pp
 hipError_t launch_gd_end(const GridC& g, const MapAux& aux, const double* pp, double* cost, hipStream_t st);
 hipError_t launch_gd_clear(unsigned* words, int n, hipStream_t st);
 int gd_update_groups(const GridC& g);

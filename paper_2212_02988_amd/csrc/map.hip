@@ -5,8 +5,9 @@
 // brick summary (one value per brick whose sign is exact: <= 0 exactly when
 // every occupancy mean of the brick is <= 0, and then not necessarily the
 // largest; the largest occupancy mean when that is > 0), a bit per brick
-// telling whether the summary is <= 0 (the renderer keeps these bits in LDS
-// to skip free space) and per-workgroup update counts.
+// telling whether the summary is <= 0, the same dilated (set when the 2x2x2
+// bricks from this one are all free: what the renderer keeps in LDS to skip
+// free space) and per-workgroup update counts.
 //
 // The map update runs in three kernels and uses no global atomics.
 //   cull:   one thread per brick tests the brick's voxel-centre box against
@@ -343,10 +344,10 @@ __global__ __launch_bounds__(256) void k_pack_bits(int nbricks, MapAux aux) {
 
 // The dilated free-space bits (second bitmap after the plain one): word w
 // is the AND of the 32-bit windows of the plain bits that start at bricks
-// 32 w + {0, 1} + {0, nb} + {0, nb^2}; words past the bitmap read as 0.  A
-// cell that spans bricks lies inside the 2x2x2 block of its base corner's
-// brick, so this one bit proves such a cell free (a cell within one brick
-// uses the plain bit).  Recomputed after every change of the plain bits.
+// 32 w + {0, 1} + {0, nb} + {0, nb^2}; words past the bitmap read as 0.  Every
+// cell, whether it spans bricks or not, lies inside the 2x2x2 block of its base
+// corner's brick, so this one bit proves it free.  Recomputed after every
+// change of the plain bits.
 __device__ __forceinline__ unsigned bits_window(const unsigned* __restrict__ bits, int nwords, int bit) {
     const int w = bit >> 5, sh = bit & 31;
     const unsigned lo = w < nwords ? bits[w] : 0u, hi = w + 1 < nwords ? bits[w + 1] : 0u;
@@ -473,12 +474,17 @@ __device__ __forceinline__ void stp(__attribute__((address_space(1))) uint16_t* 
     *(__attribute__((address_space(1))) uint16_t*)((__attribute__((address_space(1))) char*)p + i * 2u) = f2bf(v);
 }
 
-// workgroup blk of ngroups of the update.  Bound by the planes' bytes: 106 MB
-// of a 256^3 FP32 map (1.65 M voxels) take 22 us at the rate of a large copy
+// workgroup blk of ngroups of the update.  Bound by the latency of a brick's
+// chain (list, projection, depth gather, planes, stores) at four wavefronts per
+// SIMD (128 VGPRs, batched 114), warm also by the planes' bytes: 106 MB of a
+// 256^3 FP32 map (1.65 M voxels) take 22 us at the rate of a large copy
 // (4.7 TB/s), the kernel 27, of which 5 go before the first brick; 176 MB of a
 // 384^3 BF16 map 37 and 50.  16-byte accesses with all of a brick in flight
 // (27.7 / 62, 178 VGPRs) and a workgroup per brick (26.6 / 51) move them no
-// faster, nor do loads or stores past the caches (27.7, 29.7).
+// faster, nor do loads or stores past the caches (27.7, 29.7).  All of these
+// walk every brick in the frustum, about a third of which hold no voxel that the
+// frame updates, and decide in the kernel that moves the values; a separate
+// pass of decisions has not been tried.
 template <typename T, bool Pool>
 __device__ __forceinline__ void map_update_block(int blk, int ngroups, const GridC& g, const CamC& c, const GridD& gd,
                                                  T* __restrict__ map, const float* __restrict__ depth,
@@ -773,8 +779,8 @@ __global__ __launch_bounds__(256) void k_map_update_batch(BatchArgs b) {
 // The dilated bits stay good for the run's next pass without a launch over
 // them: a brick that turns occupied clears the bits of the blocks it lies in,
 // one that turns free leaves them (not proven free, which only skips less)
-// until the run's end, where the whole bitmap is formed again.  (256^3,
-// 320x240: 57 -> 47 us a step with the launch and its wait.)
+// until the run's end, where the whole bitmap is formed again.  (10 steps at
+// 256^3, 320x240: 57 -> 47 us a step without the launch and its wait.)
 __global__ __launch_bounds__(256) void k_gd_update(GridC g, float* __restrict__ map, MapAux aux,
                                                    float* __restrict__ save, double* __restrict__ grad,
                                                    const int* __restrict__ list, unsigned* __restrict__ saved,
@@ -981,12 +987,12 @@ hipError_t launch_planes(int n, int channels, const float* src, float* dst, int 
     return hipGetLastError();
 }
 
-// workgroups of the update kernel, sized to the work: a view frustum holds
-// roughly a tenth of a room's bricks, and a workgroup walks four bricks at a
-// time, so nb^3 / 32 workgroups give each wavefront about one brick (every
-// workgroup first scans the segment lengths, a fixed cost that many idle
-// workgroups would multiply); at least 64 (or every brick), at most
-// kUpdateGrid
+// workgroups of the update kernel, sized to the work: a view frustum holds 12
+// to 19 % of a room's bricks (four views of a 256^3 map: 4043-6240 of 32768),
+// and a workgroup walks four bricks at a time, so nb^3 / 32 workgroups give each
+// wavefront one or two (every workgroup first scans the segment lengths, a
+// fixed cost that many idle workgroups would multiply); at least 64 (or every
+// brick), at most kUpdateGrid
 static int update_grid(const GridC& g) {
     int nbricks = g.nb * g.nb * g.nb;
     int ng = nbricks / 32;

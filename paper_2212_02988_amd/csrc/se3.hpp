@@ -19,9 +19,9 @@ __device__ inline void mat3mul(const double A[9], const double B[9], double C[9]
 }
 
 // 1/sqrt(x) and sqrt(x) of a positive normal number: the hardware estimate
-// (about 2^-23) and two coupled Newton steps, to within an ulp or two.  The
-// pose algebra runs on one lane's dependent chain, where a square root and a
-// division cost about 300 clocks and this about 100.
+// (about 2^-23) and two steps of Goldschmidt's coupled Newton iteration, to
+// within an ulp or two.  The pose algebra runs on one lane's dependent chain,
+// where a square root and a division cost about 300 clocks and this about 100.
 __device__ __forceinline__ double rsqrt64(double x, double* root = nullptr) {
     double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;

@@ -330,9 +330,9 @@ __device__ __forceinline__ void sym_plus_outer(int n, double sign, const double*
     }
 }
 
-// 22 000 -> 9 000 clocks: the rotation's exponential comes first, and the new
-// pose (its quaternion and its relation to the anchor) is formed in the second
-// wavefront while the first inverts the pose block.
+// 9.2 -> 6.0 us: the rotation's exponential comes first, and the new pose (its
+// quaternion and its relation to the anchor) is formed in the second wavefront
+// while the first inverts the pose block.
 __device__ __forceinline__ void predict_block(prism_filter_state* __restrict__ Sg, const double* __restrict__ u,
                                               const TransC& tc, Rel32* __restrict__ rel) {
     __shared__ double T1[144], T2[144], Spp[36], Sinv[36], D[36];
@@ -568,8 +568,9 @@ __global__ __launch_bounds__(256) void k_predict(prism_filter_state* __restrict_
 // ---------------------------------------------------------------------------
 // What does not depend on the normal equations (the error of the iterate to the
 // prior, its rotation, the anchor's) is formed by the ninth wavefront while the
-// others sum them; the first then solves in registers.  16 000 -> 7 000 clocks
-// at 300 partial rows, 26 000 -> 11 000 at 1200.
+// others sum them; the first then solves in registers.  8.1 -> 4.9 us at 300
+// partial rows, 12.3 -> 8.3 at 1200 (0.4 of it for the relative pose from the
+// quaternion, whose normalisation is the recipe's, root and divisions).
 constexpr int kSolveThreads = kSumThreads + 64;
 
 struct GnPrep {
@@ -694,9 +695,9 @@ __device__ inline void combine_bias(prism_filter_state* S, prism_filter_bias_sta
     }
 }
 
-// 21 000 -> 9 000 clocks at 300 partial rows: the error of the iterate to the
-// prior is formed by the ninth wavefront while the others sum the normal
-// equations.
+// 7.9 -> 4.8 us at 300 partial rows, 12.7 -> 9.0 at 1200: the error of the
+// iterate to the prior is formed by the ninth wavefront while the others sum the
+// normal equations.
 __device__ __forceinline__ void laplace_combine_block(prism_filter_state* __restrict__ Sg,
                                                       prism_filter_bias_state* __restrict__ X,
                                                       const double* __restrict__ partials, int nblocks, double ema,

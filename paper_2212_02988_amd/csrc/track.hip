@@ -404,10 +404,10 @@ __global__ __launch_bounds__(256) void k_track_p2_batch(BatchArgs b) {
 //    step redundantly on its own copy of the iterate (a rotation matrix,
 //    converted back to a quaternion once, at the end), so a step has one
 //    workgroup barrier and nothing is handed out through memory after it.
-// 1000 steps of 200 pixels on a 320x240 frame: 5.6 -> 2.5 ms, about 5900
-// clocks a step, of which the pixel's chain takes 4100, the sums 700 and the
-// step 1250.  (Fetching the samples in the prior's wavefront took 3.1 ms: it
-// then ends last.)
+// 1000 steps of 200 pixels on a 320x240 frame: 5.6 -> 2.5 ms.  With the clock
+// read between its parts, which lengthens a step to 6350 clocks, the pixel's
+// chain takes 4100, the sums 720, the barrier 280 and the step 1250.  (Fetching
+// the samples in the prior's wavefront took 3.1 ms: it then ends last.)
 // Skipped when the prediction already fell back (improper prior).
 constexpr int kAdamThreads = 320;   // four wavefronts of pixels, one for the prior
 
