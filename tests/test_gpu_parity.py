@@ -868,6 +868,34 @@ def test_adam_sample_counts_and_step_sizes(n_pixels, n_steps, lr_r):
     assert dt_ <= 1e-5 and dr <= 1e-5
 
 
+@pytest.mark.parametrize("lr_r", [1e-5, 0.03, 0.06, 0.4, 1.2])
+def test_velocities_follow_the_pose_error(lr_r):
+    """The posterior velocities are the predicted ones plus D times the error of
+    the pose to its prior, for errors on both sides of the angle up to which the
+    rotation's logarithm is a series (one optimiser step turns by sqrt(3) lr_r:
+    1.7e-5, 0.052, 0.104, 0.69 and 2.08 rad).  Both sides start from the stored
+    quaternions; the error in double precision is below 1e-14, times the sum of
+    a row of D."""
+    banner(f"velocities after a turn of {3 ** 0.5 * lr_r:.2g} rad")
+    c = synth.trajectory_case(seed=4, n=64, width=75, height=61, n_samples=32, n_frames=2)
+    tr = c["traj"]
+    f = P().Filter(grid_of(c["scene"], 0), cam_of(c["cam"]), P().FilterParams(objective=0))
+    f.map.init()
+    f.reset(np.concatenate([tr.t[0], tr.q[0], tr.v[0], tr.w[0]]), np.diag([1e-6] * 6 + [1e-4] * 6))
+    f.step(t(c["depth"][0]), t(c["rgb"][0]), None)
+    ap = P().AdamParams.make(n_steps=1, n_pixels=64, lr_r=lr_r)
+    pix = synth.sample_pixels(20, 1, 64, c["cam"].height, c["cam"].width)
+    f.pose_update_adam(t(c["depth"][1]), t(c["rgb"][1]), t(tr.u[0], torch.float64), ap, t(pix, torch.int32))
+    s = f.state()
+    Ra, Rb = (orc.quat_to_rot(np.array(x.q)) for x in (s.iter, s.prior))
+    e = np.concatenate([np.array(s.iter.t) - np.array(s.prior.t), orc.so3_log(Ra @ Rb.T)])
+    assert abs(np.linalg.norm(e[3:]) - 3 ** 0.5 * lr_r) <= 1e-2 * lr_r
+    D = np.array(s.D).reshape(6, 6)
+    want = np.array(s.vel_prior) + D @ e
+    got = np.concatenate([np.array(s.v), np.array(s.w)])
+    assert np.all(np.abs(got - want) <= 1e-14 * (1.0 + np.abs(D).sum(1)) * max(1.0, np.abs(e).max()))
+
+
 def test_adam_rejects_p1_and_bad_samples():
     banner("adam argument checks")
     c = synth.trajectory_case(seed=2, n=64, width=80, height=60, n_samples=32, n_frames=1)
