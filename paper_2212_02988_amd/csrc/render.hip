@@ -975,14 +975,14 @@ __device__ __forceinline__ void touch_cells(const GridC& g, Scatter<V, Copies>& 
     int* const seen = reinterpret_cast<int*>(&S.win);
     for (int e = threadIdx.x & 63; e < kSlots; e += 64) seen[e] = -1;
     wave_lds_order();
-    if (!add) return;
 #pragma unroll
     for (int dz = 0; dz < 2; ++dz) {   // the four lanes of a ray take two of the eight corners each
         const int x = cl.i[0] + (s & 1), y = cl.i[1] + (s >> 1), z = cl.i[2] + dz;
-        if (max(max((unsigned)x, (unsigned)y), (unsigned)z) >= (unsigned)g.n) continue;
+        if (!add || max(max((unsigned)x, (unsigned)y), (unsigned)z) >= (unsigned)g.n) continue;
         const int bx = x >> 3, by = y >> 3, bz = z >> 3, b = (bz * g.nb + by) * g.nb + bx;
         if (atomicExch(&seen[((bz & 7) << 6) | ((by & 7) << 3) | (bx & 7)], b) != b) touched(b);
     }
+    wave_lds_order();   // the LDS is the next window's
 }
 
 // the sums of voxel (x, y, z) in window w of wavefront wv, added to sum
